@@ -172,18 +172,20 @@ void edge_constants(const Problem& pr, int axis, const float* spacing, float lam
 }
 
 // When the general edge cost's root argument fmaf(lambda, g, A_j) over the n
-// candidates' constants lies in the normal range that sqrt_rn_normal handles:
-// always when every A_j >= 2^-96 (it is at least A_j; finite image values are
-// checked on the device), and for lambda 1 (every A_j = 0, the argument is g)
-// when the device finds no small or huge image value.
-int sqrt_normal_for(const float* A, int n) {
+// candidates' constants lies in the normal range that kModeGeneralN handles:
+// when every A_j lies in [2^-96, 2^126] (the argument is at least A_j, and
+// finite since lambda g <= 16 2^122; finite image values are checked on the
+// device), and for lambda 1 (every A_j = 0, the argument is g) when the device
+// finds no small or huge image value.  (A_j that underflow to 0 at a smaller
+// lambda leave an argument of any size: the full root.)
+int sqrt_normal_for(const float* A, int n, float lam) {
   float amin = A[0], amax = A[0];
   for (int j = 1; j < n; ++j) {
     amin = A[j] < amin ? A[j] : amin;
     amax = A[j] > amax ? A[j] : amax;
   }
-  if (amin >= 0x1p-96f) return kSqrtNormalUnlessHuge;
-  return amax == 0.0f ? kSqrtNormalLam1 : kSqrtNormalNever;
+  if (amin >= 0x1p-96f && amax <= 0x1p126f) return kSqrtNormalUnlessHuge;
+  return lam == 1.0f && amax == 0.0f ? kSqrtNormalLam1 : kSqrtNormalNever;
 }
 
 int requested_mode(float lam, int C) {
@@ -341,7 +343,7 @@ int build_pass(const Problem& pr, const float* image, const float* mask, const f
   d->init = p == 0 ? 1 : 0;
   d->rec = records ? records + (size_t)p * pr.N : nullptr;
   d->epoch_base = epoch_base;
-  d->sqrt_normal = sqrt_normal_for(d->A, pr.ndim == 3 ? 9 : 3);
+  d->sqrt_normal = sqrt_normal_for(d->A, pr.ndim == 3 ? 9 : 3, lam);
   d->op = kOpPass;
   d->esz = 4;
   d->image_off = d->d_off = d->rec_off = -1;

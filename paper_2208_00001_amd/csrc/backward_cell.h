@@ -41,7 +41,7 @@ template <int MODE>
 __device__ __forceinline__ float bwd_cell_edge(const BwdDesc& g, int j, float ix, float iy) {
   const float d = ix - iy;
   if (MODE == kModeLam1C1) return fabsf(d);
-  return general_root<MODE>(fmaf(g.lam, d * d, g.A[j]));
+  return general_root<MODE, false>(fmaf(g.lam, d * d, g.A[j]));
 }
 
 // Same, offset j known only at run time.
@@ -49,7 +49,7 @@ template <int MODE>
 __device__ __forceinline__ float bwd_cell_edge_rt(const BwdDesc& g, int j, float ix, float iy) {
   const float d = ix - iy;
   if (MODE == kModeLam1C1) return fabsf(d);
-  return general_root<MODE>(fmaf(g.lam, d * d, spatial_term(g, j)));
+  return general_root<MODE, false>(fmaf(g.lam, d * d, spatial_term(g, j)));
 }
 
 template <int MODE>

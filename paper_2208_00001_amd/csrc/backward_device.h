@@ -63,7 +63,7 @@ __device__ __forceinline__ float bwd_edge(const BwdDesc& g, int j, const float* 
     const float dc = sx[c * cstride] - sy[c * cstride];
     s = fmaf(dc, dc, s);
   }
-  return general_root<MODE>(fmaf(g.lam, s, spatial_term(g, j)));
+  return general_root_any<MODE>(fmaf(g.lam, s, spatial_term(g, j)));
 }
 
 template <int NDIM, int TP, int TQ, int K, bool SCANC, int MODE, int NT = kThreads>
@@ -127,7 +127,7 @@ __device__ __forceinline__ bool run_bwd_pass(const BwdDesc* gp, unsigned long lo
               const float dc = gImage[(long long)c * g.N + x] - gImage[(long long)c * g.N + y];
               s = fmaf(dc, dc, s);
             }
-            w = general_root<MODE>(fmaf(g.lam, s, spatial_term(g, j)));
+            w = general_root_any<MODE>(fmaf(g.lam, s, spatial_term(g, j)));
           }
           if (w > 0.0f) {
             const float coef = (a * g.lam) / w;

@@ -24,7 +24,7 @@ constexpr unsigned kClassSmall = 4u;  // some image value with 0 < |I| < 2^-24 (
 // Values of PassDesc::sqrt_normal: when the general root's argument lies in
 // the normal range where kModeGeneralN's root gives sqrtf's bits.
 constexpr int kSqrtNormalNever = 0;
-constexpr int kSqrtNormalUnlessHuge = 1;  // min_j A_j >= 2^-96: fmaf(lambda, g, A_j) >= A_j
+constexpr int kSqrtNormalUnlessHuge = 1;  // every A_j in [2^-96, 2^126]: fmaf(lambda, g, A_j) >= A_j
 constexpr int kSqrtNormalLam1 = 2;        // every A_j = 0 (lambda 1): the argument is g, which is 0 or in
                                           // [2^-94, 2^126] when no image value is small or huge
 

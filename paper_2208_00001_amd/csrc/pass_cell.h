@@ -55,7 +55,7 @@ __device__ __forceinline__ float cell_edge(const PassDesc& g, int j, float ix, f
   if (MODE == kModeLam0) return g.W0[j];
   const float d = ix - iy;
   if (MODE == kModeLam1C1) return fabsf(d);
-  return general_root<MODE>(fmaf(g.lam, d * d, g.A[j]));
+  return general_root<MODE, false>(fmaf(g.lam, d * d, g.A[j]));
 }
 
 // One pass of one single-channel 3D instance by workgroup `wg` of G (blockDim

@@ -113,16 +113,36 @@ __device__ __forceinline__ int outside(int pp, int qq, int p0, int q0) {
   return max(dp, dq);
 }
 
-// Correctly rounded square root of x in [2^-96, FLT_MAX]: the hardware root
-// (within one ulp) corrected to the nearest (sqrt_round_fix).  In this range it
-// returns the bits of sqrtf as built here (the correctly rounded lowering
-// scales only arguments below 2^-96 and special-cases only zero and infinity).
-__device__ __forceinline__ float sqrt_rn_normal(float x) { return sqrt_round_fix(x, __builtin_amdgcn_sqrtf(x)); }
+// Correctly rounded square root of x in [2^-96, FLT_MAX] from the hardware's
+// reciprocal root y: g = x y is within a few ulp of the root, d = x - g^2 is
+// exact up to one rounding, and g + d y / 2 rounds to the nearest (one Newton
+// step; Markstein's form for fused multiply-add).  For the correctly rounded y
+// it gives sqrtf(x) for every x; for y one ulp off, for all but five mantissas
+// (checked on the host), and with this chip's v_rsq_f32 for every float of the
+// range (all 1.88e9 of them compared with sqrtf on the GPU; the five mantissas
+// are in the tests).  In this range sqrtf as built here has the same bits (its
+// lowering scales only arguments below 2^-96 and special-cases only zero and
+// infinity).  5 instructions instead of the 9 that correct a hardware square
+// root by the signs of two residuals (sqrt_round_fix): the general edge cost
+// is what bounds a pass at lambda in (0, 1).
+__device__ __forceinline__ float sqrt_from_rsq(float x, float y) {
+  const float g = x * y, h = 0.5f * y;
+  return fmaf(fmaf(-g, g, x), h, g);
+}
 
-// sqrtf(x) for the general modes.
-template <int MODE>
+// sqrtf(x) for the general modes.  ZERO: x may be +0 (lambda 1 with several
+// channels; then every other x is at least 2^-94): the clamped reciprocal root
+// leaves g = +0 there.
+template <int MODE, bool ZERO>
 __device__ __forceinline__ float general_root(float x) {
-  return MODE == kModeGeneralN ? sqrt_rn_normal(x) : sqrtf(x);
+  if (MODE != kModeGeneralN) return sqrtf(x);
+  return sqrt_from_rsq(x, __builtin_amdgcn_rsqf(ZERO ? fmaxf(x, 0x1p-100f) : x));
+}
+
+// The same for a channel count known only at run time (the tile kernels).
+template <int MODE>
+__device__ __forceinline__ float general_root_any(float x) {
+  return MODE == kModeGeneralN ? sqrt_round_fix(x, __builtin_amdgcn_sqrtf(x)) : sqrtf(x);
 }
 
 // A descriptor whose arrays lie in the workspace (batched launches: the
@@ -170,7 +190,7 @@ __device__ __forceinline__ float edge_cost(const PassDesc& g, int j, float ix0, 
       const float dc = sx[c * cstride] - sy[c * cstride];
       s = fmaf(dc, dc, s);
     }
-    return general_root<MODE>(fmaf(g.lam, s, g.A[j]));
+    return general_root_any<MODE>(fmaf(g.lam, s, g.A[j]));
   }
 }
 

@@ -40,7 +40,7 @@ __device__ __forceinline__ float row_edge(const PassDesc& g, int j, const float*
     const float dc = ix[c] - iy[c];
     s = fmaf(dc, dc, s);
   }
-  return general_root<MODE>(fmaf(g.lam, s, g.A[j]));
+  return general_root<MODE, (NCH > 1)>(fmaf(g.lam, s, g.A[j]));
 }
 
 // One 2D pass of an image with NCH channels (the image is not read when MODE is

@@ -379,7 +379,7 @@ __device__ __forceinline__ bool ring_sweep(const ToivDesc& d, const RingBlock& k
           const float dc = cI[c] - lds[offI + c * cs];
           g = fmaf(dc, dc, g);
         }
-        w = general_root<MODE>(fmaf(d.lam, g, d.A[k]));
+        w = general_root<MODE, (C > 1)>(fmaf(d.lam, g, d.A[k]));
       }
       const float cand = dv + w;
       if (cand < best) best = cand;

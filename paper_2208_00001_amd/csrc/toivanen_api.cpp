@@ -55,7 +55,7 @@ int make_desc(const Problem& pr, const float* image, const float* spacing, float
   // lambda 1 and one channel, else the root, in its normal-range form where
   // the argument is known to allow it
   d->mode = (lam == 1.0f && pr.C == 1) ? kModeLam1C1 : kModeGeneral;
-  d->sqrt_normal = sqrt_normal_for(d->A, n);
+  d->sqrt_normal = sqrt_normal_for(d->A, n, lam);
   return GGDT_OK;
 }
 
