@@ -216,14 +216,17 @@ size_t workspace_for(const Problem& pr, const Tuning& tu) {
 }
 
 // Bytes of one scan-major fp32 volume, and of the scan-major area of a
-// forward (D, then the image, then one pass's records, each 256-byte aligned)
-// through which the passes along the last axis of a single-channel volume run
-// as strided passes; 0 where the forward keeps those passes in place.
+// forward (D, then the image's channels, then one pass's records, each 256-byte
+// aligned) through which the passes along the last axis of a volume of up to
+// kCellMaxC channels run as strided passes; 0 where the forward keeps those
+// passes in place.
 size_t scan_major_vol_bytes(const Problem& pr) { return ((size_t)pr.N * 4 + 255) / 256 * 256; }
 
+static size_t scan_major_image_off(const Problem& pr) { return scan_major_vol_bytes(pr); }
+
 size_t scan_major_bytes(const Problem& pr) {
-  if (pr.ndim != 3 || pr.C != 1 || pr.dims[2] < 2) return 0;
-  return 2 * scan_major_vol_bytes(pr) + ((size_t)pr.N + 255) / 256 * 256;
+  if (pr.ndim != 3 || pr.C > kCellMaxC || pr.dims[2] < 2) return 0;
+  return scan_major_image_off(pr) + (((size_t)pr.C * pr.N * 4 + 255) / 256 * 256) + ((size_t)pr.N + 255) / 256 * 256;
 }
 
 // The pass along axis 2 on the scan-major copies ([W][D][H]: the scan axis
@@ -236,8 +239,18 @@ static void use_scan_major(const Problem& pr, const void* image_t, float* d_t, P
   d->sq = 1;
   d->image = static_cast<const float*>(image_t);
   d->D = d_t;
-  d->K = pass_chunk_for(pr.ndim, pr.C, d->sa == 1);
-  d->nchunk = (d->Na - 1 + d->K - 1) / d->K;
+}
+
+// The image's channels into the scan-major area.
+static hipError_t image_to_scan_major(const Problem& pr, const void* image, const ScanMajor& sm, int esz,
+                                      hipStream_t stream) {
+  for (int c = 0; c < pr.C; ++c) {
+    const size_t off = (size_t)c * pr.N * esz;
+    const hipError_t e = launch_to_scan_major((const unsigned char*)image + off, (unsigned char*)sm.image + off, esz,
+                                              pr.dims[0], pr.dims[1], pr.dims[2], nullptr, stream);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // 2D passes of images with up to kRowMaxC channels run on the row kernel
@@ -251,6 +264,37 @@ static void use_row_geometry(const Problem& pr, PassDesc* d) {
   d->ntp = 1;
   d->ntq = (d->Nq + kRowTQ - 1) / kRowTQ;
   d->nchunk = (d->Na - 1 + kRowK - 1) / kRowK;
+}
+
+// Tile of a strided thread-per-cell pass over planes of Np x Nq cells: the
+// smallest of 8 x 8, 8 x 16 and 16 x 16 whose tiles do not outnumber the
+// chip's 256 CUs.  A pass is a chain of plane steps, and a step of a smaller
+// box has fewer waves to run and to meet at its barrier, until tiles have to
+// share a CU.  us per plane, 8 x 8 / 8 x 16 / 16 x 16: at 128^3 (64 tiles of
+// 16 x 16) 0.50 / 0.53 / 0.63 at lambda 1 and 0.73 / 0.75 / 0.93 at 0.5; at
+// 187 x 145 x 93 0.90 / 0.75 / 0.93 at 0.5; at 256^3 1.85 / 0.98 / 0.64 at
+// lambda 1.  (K = 4 loses more in exchanges than it saves in halo cells: 0.62
+// at 128^3, lambda 1, and 0.77 at 256^3.)
+void cell_tile(int Np, int Nq, int* TP, int* TQ) {
+  constexpr int kCUs = 256;
+  const int tp8 = (Np + 7) / 8, tq8 = (Nq + 7) / 8, tq16 = (Nq + 15) / 16;
+  *TP = *TQ = 16;
+  if ((long long)tp8 * tq8 <= kCUs)
+    *TP = *TQ = 8;
+  else if ((long long)tp8 * tq16 <= kCUs)
+    *TP = 8;
+}
+
+// The strided passes of volumes of up to kCellMaxC channels run on the
+// thread-per-cell kernel.  (The exchange area of 16 x 16 tiles holds the smaller
+// tiles' too.)
+static void use_cell_geometry(const Problem& pr, PassDesc* d) {
+  if (pr.ndim != 3 || pr.C > kCellMaxC || d->sa == 1) return;
+  d->K = kCellK;
+  cell_tile(d->Np, d->Nq, &d->TP, &d->TQ);
+  d->ntp = (d->Np + d->TP - 1) / d->TP;
+  d->ntq = (d->Nq + d->TQ - 1) / d->TQ;
+  d->nchunk = (d->Na - 1 + d->K - 1) / d->K;
 }
 
 // Enqueue the whole forward schedule of one instance.
@@ -269,9 +313,7 @@ int enqueue_forward(const Problem& pr, const float* image, const float* mask, co
   if (launch_classify(image, (long long)pr.C * pr.N, words, stream, img_fmt) != hipSuccess) return GGDT_ERR_HIP;
   const ScanMajor sm = scan_major_for(pr, records, scan_major);
   const int esz = img_fmt == kImgF32 ? 4 : 2;
-  if (sm.on && launch_to_scan_major(image, sm.image, esz, pr.dims[0], pr.dims[1], pr.dims[2], nullptr, stream) !=
-                   hipSuccess)
-    return GGDT_ERR_HIP;
+  if (sm.on && image_to_scan_major(pr, image, sm, esz, stream) != hipSuccess) return GGDT_ERR_HIP;
   unsigned base = 0;
   const int npass = iterations * 2 * pr.ndim;
   for (int p = 0; p < npass; ++p) {
@@ -281,13 +323,14 @@ int enqueue_forward(const Problem& pr, const float* image, const float* mask, co
     d.img_fmt = img_fmt;
     use_row_geometry(pr, &d);
     d.xbuf = xbuf;
-    base += (unsigned)d.nchunk + 1u;
     const int k = p % (2 * pr.ndim);
     uint8_t* rec_c = d.rec;  // this pass's records in the array layout
     if (sm.on && k >= 4) {
       use_scan_major(pr, sm.image, sm.D, &d);
       if (rec_c) d.rec = sm.rec;  // written scan-major, moved to the array layout below
     }
+    use_cell_geometry(pr, &d);
+    base += (unsigned)d.nchunk + 1u;
     if (sm.on && k == 4 &&
         launch_to_scan_major(out, sm.D, 4, pr.dims[0], pr.dims[1], pr.dims[2], nullptr, stream) != hipSuccess)
       return GGDT_ERR_HIP;
@@ -309,8 +352,8 @@ ScanMajor scan_major_for(const Problem& pr, const uint8_t* records, void* buf) {
   if (!buf || scan_major_bytes(pr) == 0) return sm;
   sm.on = true;
   sm.D = static_cast<float*>(buf);
-  sm.image = static_cast<unsigned char*>(buf) + scan_major_vol_bytes(pr);
-  sm.rec = static_cast<uint8_t*>(buf) + 2 * scan_major_vol_bytes(pr);
+  sm.image = static_cast<unsigned char*>(buf) + scan_major_image_off(pr);
+  sm.rec = static_cast<uint8_t*>(buf) + scan_major_bytes(pr) - ((size_t)pr.N + 255) / 256 * 256;
   return sm;
 }
 
@@ -378,9 +421,7 @@ int converge_entry(int ndim, const int* dims, int C, const float* image, const f
   if (max_iterations == 0) return launch_scale(mask, v, out, pr.N, stream) == hipSuccess ? GGDT_OK : GGDT_ERR_HIP;
   if (launch_classify(image, (long long)pr.C * pr.N, words, stream) != hipSuccess) return GGDT_ERR_HIP;
   const ScanMajor sm = scan_major_for(pr, nullptr, scan_major_in(pr, tu, ws, wsb));
-  if (sm.on && launch_to_scan_major(image, sm.image, 4, pr.dims[0], pr.dims[1], pr.dims[2], nullptr, stream) !=
-                   hipSuccess)
-    return GGDT_ERR_HIP;
+  if (sm.on && image_to_scan_major(pr, image, sm, 4, stream) != hipSuccess) return GGDT_ERR_HIP;
   unsigned base = 0;
   const int per = 2 * pr.ndim;
   int block = 4;
@@ -394,9 +435,10 @@ int converge_entry(int ndim, const int* dims, int C, const float* image, const f
         use_row_geometry(pr, &d);
         d.xbuf = xbuf;
         d.converge = 1;
-        base += (unsigned)d.nchunk + 1u;
         // the layout changes do nothing once the done word is set, as the passes
         if (sm.on && k >= 4) use_scan_major(pr, sm.image, sm.D, &d);
+        use_cell_geometry(pr, &d);
+        base += (unsigned)d.nchunk + 1u;
         if (sm.on && k == 4 &&
             launch_to_scan_major(out, sm.D, 4, pr.dims[0], pr.dims[1], pr.dims[2], words + kWordDone, stream) !=
                 hipSuccess)

@@ -91,7 +91,7 @@ __global__ __launch_bounds__(kBatchThreads) void batched_kernel(const BatchInst*
       ok = run_layout_op(gp, words, lds, wg, in.nwg);
     } else if (in.ndim == 3) {
       if constexpr (CT != 0)
-        ok = run_pass_cell_rt<REC, CT, K3>(gp, xbuf, words, cls, in.mode, limit, carve_cell_lds(lds), wg, in.nwg);
+        ok = run_pass_cell_rt<REC, CellGeom<CT, CT, K3>>(gp, xbuf, words, cls, in.mode, limit, carve_cell_lds(lds), wg, in.nwg);
       else
         ok = run_pass_rt<3, kTP3, kTQ3, K3, REC>(gp, xbuf, words, cls, in.mode, limit, lds, wg, in.nwg);
     } else {

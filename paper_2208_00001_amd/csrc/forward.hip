@@ -1,7 +1,7 @@
 // Forward directional-pass kernels for gfx950: one launch per pass of one
 // instance (see pass_device.h for the pass itself), plus the small helper
 // kernels (workspace reset, image classification, v * M).
-#include "pass_cell.h"
+#include "cell_kernels.h"
 #include "pass_device.h"
 #include "pass_row.h"
 
@@ -19,27 +19,6 @@ __global__ __launch_bounds__(kThreads) void pass_kernel(PassDesc g, unsigned* wo
                                                     xcd_remap(blockIdx.x, gridDim.x), gridDim.x);
 }
 
-// Single-channel 3D passes on 16 x 16 tiles with K = 8: one thread per box cell.
-template <bool SCANC, int RMODE, bool REC, int FMT = kImgF32>
-__global__ __launch_bounds__(kCellThreads) void pass_cell_kernel(PassDesc g, unsigned* words,
-                                                                 unsigned long long limit) {
-  __shared__ float2 pair[2 * kCellThreads];
-  __shared__ int fail;
-  CellLds lds{pair, nullptr, nullptr, nullptr, &fail};
-  if constexpr (SCANC) {
-    __shared__ float stD[kCellStage];
-    __shared__ float stI[kCellStage];
-    __shared__ float res[kCellTP * kCellTQ * kCellSCR];
-    lds.stD = stD;
-    lds.stI = stI;
-    lds.res = res;
-  }
-  if (ld_relaxed(words + kWordAbort) != 0u) return;
-  if (g.converge && ld_relaxed(words + kWordDone) != 0u) return;  // an earlier iteration changed nothing
-  run_pass_cell_mode<SCANC, RMODE, REC, kCellTP, kCellK, FMT>(&g, g.xbuf, words, words + kWordClass, limit, lds,
-                                                             xcd_remap(blockIdx.x, gridDim.x), gridDim.x);
-}
-
 // 2D passes of images with up to kRowMaxC channels: one wave per 32-cell tile.
 template <int RMODE, int NCH, bool REC, int FMT = kImgF32>
 __global__ __launch_bounds__(kRowLanes) void pass_row_kernel(PassDesc g, unsigned* words, unsigned long long limit) {
@@ -48,8 +27,6 @@ __global__ __launch_bounds__(kRowLanes) void pass_row_kernel(PassDesc g, unsigne
   run_pass_row_mode<RMODE, NCH, REC, FMT>(&g, g.xbuf, words, words + kWordClass, limit,
                                           xcd_remap(blockIdx.x, gridDim.x), gridDim.x);
 }
-
-using PassKernel = void (*)(PassDesc, unsigned*, unsigned long long);
 
 bool use_row_path(const PassDesc& d, int ndim) {
   return ndim == 2 && d.TP == 1 && d.TQ == kRowTQ && d.K == kRowK && d.C >= 1 && d.C <= kRowMaxC && d.ntp == 1;
@@ -76,35 +53,9 @@ PassKernel select_row_kernel(const PassDesc& d) {
   return d.rec ? select_row_channels<true>(d) : select_row_channels<false>(d);
 }
 
-bool use_cell_path(const PassDesc& d, int ndim) {
-  return ndim == 3 && d.C == 1 && d.TP == kCellTP && d.TQ == kCellTQ && d.K == kCellK;
-}
-
-template <bool SCANC, int FMT>
-PassKernel select_cell_fmt(const PassDesc& d) {
-  if (d.rec) return nullptr;
-  if (d.mode == kModeLam0) return pass_cell_kernel<SCANC, kModeLam0, false, FMT>;
-  if (d.mode == kModeLam1C1) return pass_cell_kernel<SCANC, kModeLam1C1, false, FMT>;
-  return pass_cell_kernel<SCANC, kModeGeneral, false, FMT>;
-}
-
-template <bool SCANC>
-PassKernel select_cell_mode(const PassDesc& d) {
-  // 16-bit images: plain forward passes only (no records)
-  if (d.img_fmt == kImgBF16) return select_cell_fmt<SCANC, kImgBF16>(d);
-  if (d.img_fmt == kImgF16) return select_cell_fmt<SCANC, kImgF16>(d);
-  if (d.rec) {
-    if (d.mode == kModeLam0) return pass_cell_kernel<SCANC, kModeLam0, true>;
-    if (d.mode == kModeLam1C1) return pass_cell_kernel<SCANC, kModeLam1C1, true>;
-    return pass_cell_kernel<SCANC, kModeGeneral, true>;
-  }
-  if (d.mode == kModeLam0) return pass_cell_kernel<SCANC, kModeLam0, false>;
-  if (d.mode == kModeLam1C1) return pass_cell_kernel<SCANC, kModeLam1C1, false>;
-  return pass_cell_kernel<SCANC, kModeGeneral, false>;
-}
-
-PassKernel select_cell_kernel(const PassDesc& d) {
-  return d.sa == 1 ? select_cell_mode<true>(d) : select_cell_mode<false>(d);
+bool use_cell_path(const PassDesc& d) {
+  const bool tile = (d.TP == 16 && d.TQ == 16) || (d.sa != 1 && d.TP == 8 && (d.TQ == 16 || d.TQ == 8));
+  return tile && d.C == 1;
 }
 
 template <int NDIM, int TP, int TQ, int K, bool SCANC>
@@ -259,14 +210,17 @@ hipError_t launch_pass(const PassDesc& d, int ndim, unsigned* words, unsigned lo
     hipLaunchKernelGGL(fn, dim3(grid), dim3(kRowLanes), 0, stream, d, words, spin_limit);
     return hipGetLastError();
   }
-  if (use_cell_path(d, ndim)) {
-    PassKernel fn = select_cell_kernel(d);
+  if (ndim == 3 && d.K == kCellK && use_cell_path(d)) {
+    const int geo = d.TP == 16 ? 0 : (d.TQ == 16 ? 1 : 2);
+    PassKernel fn = geo == 0 ? cell_kernel_base(d) : (geo == 1 ? cell_kernel_mid(d) : cell_kernel_small(d));
     if (!fn) return hipErrorInvalidConfiguration;
-    const int cap = capacity_for(fn, 0, kCellThreads);
+    constexpr int threads[3] = {CellGeomBase::NT, CellGeomMid::NT, CellGeomSmall::NT};
+    constexpr int threads_cap[3] = {CellGeomBase::NTCAP, CellGeomMid::NTCAP, CellGeomSmall::NTCAP};
+    const int cap = capacity_for(fn, 0, threads_cap[geo]);
     if (cap <= 0) return hipErrorInvalidConfiguration;
     const int ntiles = d.ntp * d.ntq;
     const int grid = ntiles < cap ? ntiles : cap;
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(kCellThreads), 0, stream, d, words, spin_limit);
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(threads[geo]), 0, stream, d, words, spin_limit);
     return hipGetLastError();
   }
   if (d.img_fmt != kImgF32) return hipErrorInvalidConfiguration;  // 16-bit images: cell and row kernels only

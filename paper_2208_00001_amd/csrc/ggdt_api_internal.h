@@ -48,6 +48,7 @@ int check_params(int ndim, const float* spacing, float v, float lam, int iterati
 int check_alias(const void* out, size_t nout, const void* const* ins, const size_t* nins, int nin);
 void tile_shape(const Problem& pr, const Tuning& tu, int* TP, int* TQ);
 void pass_geometry(const Problem& pr, int axis, PassDesc* d);
+void cell_tile(int Np, int Nq, int* TP, int* TQ);
 void edge_constants(const Problem& pr, int axis, const float* spacing, float lam, float* A, float* W0);
 int sqrt_normal_for(const float* A, int n, float lam);  // kSqrtNormal* for the constants A_0..A_{n-1}
 int requested_mode(float lam, int C);
@@ -56,13 +57,13 @@ int build_bwd_pass(const Problem& pr, const float* image, const uint8_t* records
                    float* gI, int p, int K, unsigned epoch_base, BwdDesc* d);
 size_t workspace_for(const Problem& pr, const Tuning& tu);
 // Scan-major copies of D and of the image for the passes along the last axis
-// of a single-channel volume (see layout.hip).
+// of a volume of up to kCellMaxC channels (see layout.hip).
 size_t scan_major_bytes(const Problem& pr);
 size_t scan_major_vol_bytes(const Problem& pr);  // one fp32 volume, 256-byte aligned
 struct ScanMajor {
   bool on;
   float* D;      // D laid out [W][D][H]
-  void* image;   // the image in its storage format, laid out [W][D][H]
+  void* image;   // the image in its storage format, each channel laid out [W][D][H]
   uint8_t* rec;  // one pass's records laid out [W][D][H] (forward with records)
 };
 // The copies in `buf` (scan_major_bytes(pr) bytes), if the schedule uses them.
@@ -73,7 +74,7 @@ void* scan_major_in(const Problem& pr, const Tuning& tu, void* ws, size_t wsb);
 // Enqueue the whole forward schedule of one instance on `stream` (arguments
 // already validated; ws holds at least workspace_for(pr, tu) bytes).  With
 // `scan_major` (scan_major_bytes(pr) bytes, or null) the passes along the last
-// axis of a single-channel volume without records run on scan-major copies.
+// axis of a volume of up to kCellMaxC channels run on scan-major copies.
 int enqueue_forward(const Problem& pr, const float* image, const float* mask, const float* spacing, float v,
                     float lam, int iterations, float* out, uint8_t* records, void* ws, const Tuning& tu,
                     hipStream_t stream, int img_fmt = kImgF32, void* scan_major = nullptr);

@@ -169,6 +169,10 @@ constexpr int kTP3 = 16, kTQ3 = 16, kTQ2 = 256;
 // kRowTQ = 64 - 2 kRowK owned cells per tile, images of up to kRowMaxC channels.
 constexpr int kRowLanes = 64, kRowK = 16, kRowTQ = kRowLanes - 2 * kRowK, kRowMaxC = 3;
 
+// Thread-per-cell 3D passes (pass_cell.h): the widest tile geometry, and the
+// channels they take.
+constexpr int kCellTP = 16, kCellTQ = 16, kCellK = 8, kCellMaxC = 1;
+
 // Batched kernel classes: 0 for single-channel batches (3D: thread-per-cell
 // pass on 16 x 16 tiles, K = 8); 1 for up to 4 channels (tile passes, K = 4 /
 // 16); 2 single-channel, chosen by tuning (3D: thread-per-cell pass on 24 x 24

@@ -1,17 +1,18 @@
 // Device code of one 3D directional pass with one thread per cell of the tile
 // box (single-channel images).
 //
-// Same decomposition as run_pass in pass_device.h: the plane is cut into
-// 16 x 16 tiles owned by workgroups, the scan axis into chunks of K = 8 steps,
-// and each chunk recomputes a halo that shrinks by one voxel per plane, so that
-// neighbours are consulted only between chunks, through epoch-tagged exchange
-// words.  The mapping differs: a workgroup of 1024 threads covers the tile's
-// 32 x 32 box (the tile grown by K on each side) with one thread per box cell,
-// fixed for the whole pass.  A thread holds its cell's image and D_old values
-// for the chunk's planes in registers, loaded straight from global memory; the
-// only LDS traffic is the previous plane's (D, I) pairs, read at fixed offsets.
-// At step i of a chunk the cells within Chebyshev distance kk - 1 - i of the
-// tile compute; the others idle.
+// Same decomposition as run_pass in pass_device.h: the plane is cut into tiles
+// owned by workgroups, the scan axis into chunks of K = 8 steps, and each chunk
+// recomputes a halo that shrinks by one voxel per plane, so that neighbours are
+// consulted only between chunks, through epoch-tagged exchange words.  The
+// mapping differs: a workgroup covers the tile's box (the tile grown by K on
+// each side) with one thread per box cell, fixed for the whole pass: 1024
+// threads for a 16 x 16 tile, 768 for 8 x 16, 576 for 8 x 8 (cell_tile in
+// api.cpp chooses).  A thread holds its cell's image and D_old values for the
+// chunk's planes in registers, loaded straight from global memory; the only LDS
+// traffic is the previous plane's (D, I) pairs, read at fixed offsets.  At step
+// i of a chunk the cells within Chebyshev distance kk - 1 - i of the tile
+// compute; the others idle.
 #pragma once
 
 #include "pass_device.h"
@@ -19,7 +20,7 @@
 namespace ggdt {
 namespace dev {
 
-constexpr int kCellTP = 16, kCellTQ = 16, kCellK = 8;
+
 constexpr int kCellBQ = kCellTQ + 2 * kCellK;          // 32: box row length
 constexpr int kCellThreads = kCellBQ * kCellBQ;         // 1024: one thread per box cell
 // Scan-contiguous layout: per box cell a run of kCellSC consecutive memory
@@ -29,21 +30,30 @@ constexpr int kCellSC = 4 * ((kCellK + 4 + 3) / 4);    // 12
 constexpr int kCellSCR = kCellK + 1;                     // 9
 constexpr int kCellStage = kCellThreads * kCellSC;       // floats of one staged array
 
-// The same box of 1024 cells also holds a 24 x 24 tile with K = 4 (batched
-// launches may choose it): 1.27 computed cells per voxel update instead of
-// 2.15, for twice the exchanges.
-template <int TT, int KC>
+// Tile, chunk and box of a pass, and the threads of its workgroups.
+template <int TP_, int TQ_, int KC>
 struct CellGeom {
-  static constexpr int TP = TT, TQ = TT, K = KC;
-  static constexpr int BQ = TT + 2 * KC;
-  static constexpr int NB = BQ * BQ;
+  static constexpr int TP = TP_, TQ = TQ_, K = KC;
+  static constexpr int BP = TP_ + 2 * KC, BQ = TQ_ + 2 * KC;
+  static constexpr int NB = BP * BQ;
+  static constexpr int NT = (NB + 63) / 64 * 64;
+  // Threads to ask the occupancy query with: a workgroup's waves may all need
+  // room on ceil(waves / 4) slots of one SIMD, which a count that is no
+  // multiple of 4 waves would not show.
+  static constexpr int NTCAP = (NB + 255) / 256 * 256;
   static constexpr int SC = 4 * ((KC + 4 + 3) / 4);
   static constexpr int SCR = KC + 1;
   static constexpr int STAGE = NB * SC;
-  static constexpr int RES = TT * TT * SCR;
-  static_assert(NB == kCellThreads, "one thread per cell of a 32 x 32 box");
+  static constexpr int RES = TP_ * TQ_ * SCR;
+  static_assert(NT <= kCellThreads, "one thread per box cell");
 };
-using CellGeomWide = CellGeom<24, 4>;
+using CellGeomBase = CellGeom<kCellTP, kCellTQ, kCellK>;
+using CellGeomMid = CellGeom<8, 16, kCellK>;    // 24 x 32 box, 12 waves
+using CellGeomSmall = CellGeom<8, 8, kCellK>;   // 24 x 24 box, 9 waves
+// The same box of 1024 cells also holds a 24 x 24 tile with K = 4 (batched
+// launches may choose it): 1.27 computed cells per voxel update instead of
+// 2.15, for twice the exchanges.
+using CellGeomWide = CellGeom<24, 24, 4>;
 constexpr int kCellWideTP = CellGeomWide::TP, kCellWideK = CellGeomWide::K;
 // largest staged array and result buffer over the geometries
 constexpr int kCellStageMax = kCellStage > CellGeomWide::STAGE ? kCellStage : CellGeomWide::STAGE;
@@ -102,11 +112,11 @@ __device__ __forceinline__ CellLds carve_cell_lds(float* lds) {
   return l;
 }
 
-template <bool SCANC, int MODE, bool REC, int TT = kCellTP, int KC = kCellK, int FMT = kImgF32>
+template <bool SCANC, int MODE, bool REC, class Geo = CellGeomBase, int FMT = kImgF32>
 __device__ __forceinline__ bool run_pass_cell(const PassDesc* gp, unsigned long long* xbuf, unsigned* words,
                                               unsigned long long limit, const CellLds& lds, int wg, int G) {
-  using Geo = CellGeom<TT, KC>;
   constexpr int TP = Geo::TP, TQ = Geo::TQ, K = Geo::K, BQ = Geo::BQ, NB = Geo::NB;
+  static_assert(!SCANC || NB == Geo::NT, "the staging loops give every thread a cell");
   constexpr int SC = Geo::SC, SCR = Geo::SCR, STAGE = Geo::STAGE;
   const PassDesc g = resolve_offsets(*gp, words);
   // global-memory views of the descriptor's arrays (the image in its storage format)
@@ -128,7 +138,7 @@ __device__ __forceinline__ bool run_pass_cell(const PassDesc* gp, unsigned long 
   const int Na = g.Na, Np = g.Np, Nq = g.Nq;
   constexpr bool USE_I = MODE != kModeLam0;
   float2* const P0 = lds.pair;
-  float2* const P1 = P0 + NB;
+  float2* const P1 = P0 + Geo::NT;
   float* const StD = lds.stD;
   float* const StI = lds.stI;
   float* const Res = lds.res;
@@ -394,25 +404,7 @@ __device__ __forceinline__ bool run_pass_cell(const PassDesc* gp, unsigned long 
         const int slot = (cur.pp - otp * TP) * TQ + (cur.qq - otq * TQ);
         const unsigned long long* a =
             xbuf + (size_t)((c - 1) & 1) * ntiles * (TP * TQ) + (size_t)(otp * g.ntq + otq) * (TP * TQ) + slot;
-        unsigned long long wv = ld64_relaxed(a);
-        unsigned long long polls = 0;
-        while ((unsigned)(wv >> 32) != epoch_in) {
-          // the abort word costs a memory round trip: look at it every 32 polls
-          if ((++polls & 31u) == 0u) {
-            if (ld_relaxed(words + kWordAbort) != 0u) {
-              fail = 1;
-              break;
-            }
-            if (polls > limit) {
-              __hip_atomic_fetch_or(words + kWordAbort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              fail = 1;
-              break;
-            }
-          }
-          __builtin_amdgcn_s_sleep(1);
-          wv = ld64_relaxed(a);
-        }
-        d0 = __uint_as_float((unsigned)wv);
+        d0 = wait_word(a, epoch_in, words, limit, &fail);
       }
     }
     // Cells outside the volume hold +inf in both planes, so candidates through
@@ -505,37 +497,37 @@ __device__ __forceinline__ bool run_pass_cell(const PassDesc* gp, unsigned long 
 
 // Requested mode RMODE falls back to the general formula when the image
 // classification word rules the fast edge cost out.
-template <bool SCANC, int RMODE, bool REC, int TT = kCellTP, int KC = kCellK, int FMT = kImgF32>
+template <bool SCANC, int RMODE, bool REC, class Geo = CellGeomBase, int FMT = kImgF32>
 __device__ __forceinline__ bool run_pass_cell_mode(const PassDesc* gp, unsigned long long* xbuf, unsigned* words,
                                                    const unsigned* cls_word, unsigned long long limit,
                                                    const CellLds& lds, int wg, int G) {
   if (RMODE == kModeGeneral) {
     if (general_n_ok(gp->sqrt_normal, cls_word))
-      return run_pass_cell<SCANC, kModeGeneralN, REC, TT, KC, FMT>(gp, xbuf, words, limit, lds, wg, G);
-    return run_pass_cell<SCANC, kModeGeneral, REC, TT, KC, FMT>(gp, xbuf, words, limit, lds, wg, G);
+      return run_pass_cell<SCANC, kModeGeneralN, REC, Geo, FMT>(gp, xbuf, words, limit, lds, wg, G);
+    return run_pass_cell<SCANC, kModeGeneral, REC, Geo, FMT>(gp, xbuf, words, limit, lds, wg, G);
   }
   const bool fast = fast_mode_ok(RMODE, ld_relaxed(cls_word));
-  if (fast) return run_pass_cell<SCANC, RMODE, REC, TT, KC, FMT>(gp, xbuf, words, limit, lds, wg, G);
-  return run_pass_cell<SCANC, kModeGeneral, REC, TT, KC, FMT>(gp, xbuf, words, limit, lds, wg, G);
+  if (fast) return run_pass_cell<SCANC, RMODE, REC, Geo, FMT>(gp, xbuf, words, limit, lds, wg, G);
+  return run_pass_cell<SCANC, kModeGeneral, REC, Geo, FMT>(gp, xbuf, words, limit, lds, wg, G);
 }
 
 // Layout and requested mode chosen at run time (batched launches).
-template <bool REC, int TT = kCellTP, int KC = kCellK>
+template <bool REC, class Geo = CellGeomBase>
 __device__ __forceinline__ bool run_pass_cell_rt(const PassDesc* gp, unsigned long long* xbuf, unsigned* words,
                                                  const unsigned* cls_word, int mode, unsigned long long limit,
                                                  const CellLds& lds, int wg, int G) {
   if (gp->sa == 1) {
     if (mode == kModeLam0)
-      return run_pass_cell_mode<true, kModeLam0, REC, TT, KC>(gp, xbuf, words, cls_word, limit, lds, wg, G);
+      return run_pass_cell_mode<true, kModeLam0, REC, Geo>(gp, xbuf, words, cls_word, limit, lds, wg, G);
     if (mode == kModeLam1C1)
-      return run_pass_cell_mode<true, kModeLam1C1, REC, TT, KC>(gp, xbuf, words, cls_word, limit, lds, wg, G);
-    return run_pass_cell_mode<true, kModeGeneral, REC, TT, KC>(gp, xbuf, words, cls_word, limit, lds, wg, G);
+      return run_pass_cell_mode<true, kModeLam1C1, REC, Geo>(gp, xbuf, words, cls_word, limit, lds, wg, G);
+    return run_pass_cell_mode<true, kModeGeneral, REC, Geo>(gp, xbuf, words, cls_word, limit, lds, wg, G);
   }
   if (mode == kModeLam0)
-    return run_pass_cell_mode<false, kModeLam0, REC, TT, KC>(gp, xbuf, words, cls_word, limit, lds, wg, G);
+    return run_pass_cell_mode<false, kModeLam0, REC, Geo>(gp, xbuf, words, cls_word, limit, lds, wg, G);
   if (mode == kModeLam1C1)
-    return run_pass_cell_mode<false, kModeLam1C1, REC, TT, KC>(gp, xbuf, words, cls_word, limit, lds, wg, G);
-  return run_pass_cell_mode<false, kModeGeneral, REC, TT, KC>(gp, xbuf, words, cls_word, limit, lds, wg, G);
+    return run_pass_cell_mode<false, kModeLam1C1, REC, Geo>(gp, xbuf, words, cls_word, limit, lds, wg, G);
+  return run_pass_cell_mode<false, kModeGeneral, REC, Geo>(gp, xbuf, words, cls_word, limit, lds, wg, G);
 }
 
 }  // namespace dev

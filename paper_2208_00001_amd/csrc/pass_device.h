@@ -94,6 +94,30 @@ __device__ __forceinline__ void st64_relaxed(unsigned long long* p, unsigned lon
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The value of the word at `a` once it is published under `epoch`: polled up to
+// `limit` times, then the abort word is set; *fail when the wait gave up.
+__device__ __forceinline__ float wait_word(const unsigned long long* a, unsigned epoch, unsigned* words,
+                                           unsigned long long limit, int* fail) {
+  unsigned long long wv = ld64_relaxed(a);
+  unsigned long long polls = 0;
+  while ((unsigned)(wv >> 32) != epoch) {
+    ++polls;
+    if (polls > limit) {
+      __hip_atomic_fetch_or(words + kWordAbort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      *fail = 1;
+      break;
+    }
+    // the abort word costs a memory round trip: look at it every 32 polls
+    if ((polls & 31u) == 0u && ld_relaxed(words + kWordAbort) != 0u) {
+      *fail = 1;
+      break;
+    }
+    __builtin_amdgcn_s_sleep(1);
+    wv = ld64_relaxed(a);
+  }
+  return __uint_as_float((unsigned)wv);
+}
+
 // Workgroup barrier that orders LDS only.  Steps inside a chunk exchange values
 // through LDS; their global stores are read by nobody in the workgroup, so the
 // barrier must not wait for them (a full __syncthreads would put a store round

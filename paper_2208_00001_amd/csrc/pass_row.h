@@ -175,24 +175,7 @@ __device__ __forceinline__ bool run_pass_row(const PassDesc* gp, unsigned long l
       } else {
         // the owner's slot of cell q is q itself: tile q / TQ, slot q % TQ
         const unsigned long long* a = xbuf + (size_t)((c - 1) & 1) * ntiles * TQ + cur.q;
-        unsigned long long wv = ld64_relaxed(a);
-        unsigned long long polls = 0;
-        while ((unsigned)(wv >> 32) != epoch_in) {
-          if ((++polls & 31u) == 0u) {
-            if (ld_relaxed(words + kWordAbort) != 0u) {
-              fail = 1;
-              break;
-            }
-            if (polls > limit) {
-              __hip_atomic_fetch_or(words + kWordAbort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              fail = 1;
-              break;
-            }
-          }
-          __builtin_amdgcn_s_sleep(1);
-          wv = ld64_relaxed(a);
-        }
-        dcur = __uint_as_float((unsigned)wv);
+        dcur = wait_word(a, epoch_in, words, limit, &fail);
       }
     }
     if (__any(fail)) return false;
