@@ -10,12 +10,16 @@ using PassKernel = void (*)(PassDesc, unsigned*, unsigned long long);
 
 namespace dev {
 
-// Single-channel 3D passes: one thread per box cell.
-template <class Geo, bool SCANC, int RMODE, bool REC, int FMT>
+// One thread per box cell.
+template <class Geo, bool SCANC, int RMODE, bool REC, int FMT, int NCH>
 __global__ __launch_bounds__(Geo::NTCAP) void pass_cell_kernel(PassDesc g, unsigned* words, unsigned long long limit) {
   __shared__ float2 pair[2 * Geo::NT];
   __shared__ int fail;
-  CellLds lds{pair, nullptr, nullptr, nullptr, &fail};
+  CellLds lds{pair, nullptr, nullptr, nullptr, nullptr, &fail};
+  if constexpr (NCH > 1) {  // (lambda 0 too: it falls back to the general cost)
+    __shared__ float chan[2 * (NCH - 1) * Geo::NT];
+    lds.chan = chan;
+  }
   if constexpr (SCANC) {
     __shared__ float stD[Geo::STAGE];
     __shared__ float stI[Geo::STAGE];
@@ -26,15 +30,15 @@ __global__ __launch_bounds__(Geo::NTCAP) void pass_cell_kernel(PassDesc g, unsig
   }
   if (ld_relaxed(words + kWordAbort) != 0u) return;
   if (g.converge && ld_relaxed(words + kWordDone) != 0u) return;  // an earlier iteration changed nothing
-  run_pass_cell_mode<SCANC, RMODE, REC, Geo, FMT>(&g, g.xbuf, words, words + kWordClass, limit, lds,
+  run_pass_cell_mode<SCANC, RMODE, REC, Geo, FMT, NCH>(&g, g.xbuf, words, words + kWordClass, limit, lds,
                                                   xcd_remap(blockIdx.x, gridDim.x), gridDim.x);
 }
 
-template <class Geo, bool SCANC, bool REC, int FMT>
+template <class Geo, bool SCANC, bool REC, int FMT, int NCH = 1>
 PassKernel cell_kernel_mode(int mode) {
-  if (mode == kModeLam0) return pass_cell_kernel<Geo, SCANC, kModeLam0, REC, FMT>;
-  if (mode == kModeLam1C1) return pass_cell_kernel<Geo, SCANC, kModeLam1C1, REC, FMT>;
-  return pass_cell_kernel<Geo, SCANC, kModeGeneral, REC, FMT>;
+  if (mode == kModeLam0) return pass_cell_kernel<Geo, SCANC, kModeLam0, REC, FMT, NCH>;
+  if (NCH == 1 && mode == kModeLam1C1) return pass_cell_kernel<Geo, SCANC, kModeLam1C1, REC, FMT, 1>;
+  return pass_cell_kernel<Geo, SCANC, kModeGeneral, REC, FMT, NCH>;
 }
 
 // 16-bit images: plain forward passes only (no records).
@@ -49,11 +53,19 @@ PassKernel cell_kernel_for(const PassDesc& d) {
                : cell_kernel_mode<Geo, SCANC, false, kImgF32>(d.mode);
 }
 
+// Multi-channel volumes, strided passes.
+template <class Geo, int NCH>
+PassKernel cell_kernel_channels(const PassDesc& d) {
+  return d.rec ? cell_kernel_mode<Geo, false, true, kImgF32, NCH>(d.mode)
+               : cell_kernel_mode<Geo, false, false, kImgF32, NCH>(d.mode);
+}
+
 }  // namespace dev
 
 // The kernel of a pass on its tile geometry, by source file; null if there is none.
 PassKernel cell_kernel_base(const PassDesc& d);
 PassKernel cell_kernel_mid(const PassDesc& d);
 PassKernel cell_kernel_small(const PassDesc& d);
+PassKernel cell_kernel_multi(const PassDesc& d);
 
 }  // namespace ggdt

@@ -53,9 +53,10 @@ PassKernel select_row_kernel(const PassDesc& d) {
   return d.rec ? select_row_channels<true>(d) : select_row_channels<false>(d);
 }
 
+// Volumes of up to kCellMaxC channels; with several channels the strided passes only.
 bool use_cell_path(const PassDesc& d) {
   const bool tile = (d.TP == 16 && d.TQ == 16) || (d.sa != 1 && d.TP == 8 && (d.TQ == 16 || d.TQ == 8));
-  return tile && d.C == 1;
+  return tile && (d.C == 1 || (d.C <= kCellMaxC && d.sa != 1));
 }
 
 template <int NDIM, int TP, int TQ, int K, bool SCANC>
@@ -212,7 +213,8 @@ hipError_t launch_pass(const PassDesc& d, int ndim, unsigned* words, unsigned lo
   }
   if (ndim == 3 && d.K == kCellK && use_cell_path(d)) {
     const int geo = d.TP == 16 ? 0 : (d.TQ == 16 ? 1 : 2);
-    PassKernel fn = geo == 0 ? cell_kernel_base(d) : (geo == 1 ? cell_kernel_mid(d) : cell_kernel_small(d));
+    PassKernel fn = d.C > 1 ? cell_kernel_multi(d)
+                            : (geo == 0 ? cell_kernel_base(d) : (geo == 1 ? cell_kernel_mid(d) : cell_kernel_small(d)));
     if (!fn) return hipErrorInvalidConfiguration;
     constexpr int threads[3] = {CellGeomBase::NT, CellGeomMid::NT, CellGeomSmall::NT};
     constexpr int threads_cap[3] = {CellGeomBase::NTCAP, CellGeomMid::NTCAP, CellGeomSmall::NTCAP};

@@ -171,7 +171,7 @@ constexpr int kRowLanes = 64, kRowK = 16, kRowTQ = kRowLanes - 2 * kRowK, kRowMa
 
 // Thread-per-cell 3D passes (pass_cell.h): the widest tile geometry, and the
 // channels they take.
-constexpr int kCellTP = 16, kCellTQ = 16, kCellK = 8, kCellMaxC = 1;
+constexpr int kCellTP = 16, kCellTQ = 16, kCellK = 8, kCellMaxC = 3;
 
 // Batched kernel classes: 0 for single-channel batches (3D: thread-per-cell
 // pass on 16 x 16 tiles, K = 8); 1 for up to 4 channels (tile passes, K = 4 /

@@ -60,12 +60,19 @@ constexpr int kCellStageMax = kCellStage > CellGeomWide::STAGE ? kCellStage : Ce
 constexpr int kCellResMax = kCellTP * kCellTQ * kCellSCR > CellGeomWide::RES ? kCellTP * kCellTQ * kCellSCR
                                                                                 : CellGeomWide::RES;
 
-template <int MODE>
-__device__ __forceinline__ float cell_edge(const PassDesc& g, int j, float ix, float iy) {
+// Edge cost through offset j from the channels of x (ix) and of its parent (iy).
+template <int MODE, int NCH>
+__device__ __forceinline__ float cell_edge(const PassDesc& g, int j, const float* ix, const float* iy) {
   if (MODE == kModeLam0) return g.W0[j];
-  const float d = ix - iy;
+  const float d = ix[0] - iy[0];
   if (MODE == kModeLam1C1) return fabsf(d);
-  return general_root<MODE, false>(fmaf(g.lam, d * d, g.A[j]));
+  float s = d * d;
+#pragma unroll
+  for (int c = 1; c < NCH; ++c) {
+    const float dc = ix[c] - iy[c];
+    s = fmaf(dc, dc, s);
+  }
+  return general_root<MODE, (NCH > 1)>(fmaf(g.lam, s, g.A[j]));
 }
 
 // One pass of one single-channel 3D instance by workgroup `wg` of G (blockDim
@@ -88,7 +95,8 @@ __device__ __forceinline__ void step_barrier() {
 // then provably do not alias the pair planes, and the steps need not wait for
 // them to land.
 struct CellLds {
-  float2* pair;  // 2 x kCellThreads
+  float2* pair;  // 2 x threads: (D, I of channel 0)
+  float* chan;   // 2 x (NCH - 1) x threads: the further channels (multi-channel volumes only)
   float* stD;    // kCellStage (scan-contiguous layout only)
   float* stI;    // kCellStage
   float* res;    // kCellTP * kCellTQ * kCellSCR
@@ -105,6 +113,7 @@ constexpr size_t kCellLdsBytes = sizeof(float2) * 2 * kCellThreads +
 __device__ __forceinline__ CellLds carve_cell_lds(float* lds) {
   CellLds l;
   l.pair = reinterpret_cast<float2*>(lds);
+  l.chan = nullptr;
   l.stD = lds + 4 * kCellThreads;
   l.stI = l.stD + kCellStageMax;
   l.res = l.stI + kCellStageMax;
@@ -112,11 +121,12 @@ __device__ __forceinline__ CellLds carve_cell_lds(float* lds) {
   return l;
 }
 
-template <bool SCANC, int MODE, bool REC, class Geo = CellGeomBase, int FMT = kImgF32>
+template <bool SCANC, int MODE, bool REC, class Geo = CellGeomBase, int FMT = kImgF32, int NCH = 1>
 __device__ __forceinline__ bool run_pass_cell(const PassDesc* gp, unsigned long long* xbuf, unsigned* words,
                                               unsigned long long limit, const CellLds& lds, int wg, int G) {
   constexpr int TP = Geo::TP, TQ = Geo::TQ, K = Geo::K, BQ = Geo::BQ, NB = Geo::NB;
-  static_assert(!SCANC || NB == Geo::NT, "the staging loops give every thread a cell");
+  static_assert(!SCANC || (NB == Geo::NT && NCH == 1), "the staging loops give every thread a cell of one channel");
+  static_assert(FMT == kImgF32 || NCH == 1, "16-bit volumes have one channel");
   constexpr int SC = Geo::SC, SCR = Geo::SCR, STAGE = Geo::STAGE;
   const PassDesc g = resolve_offsets(*gp, words);
   // global-memory views of the descriptor's arrays (the image in its storage format)
@@ -139,6 +149,9 @@ __device__ __forceinline__ bool run_pass_cell(const PassDesc* gp, unsigned long 
   constexpr bool USE_I = MODE != kModeLam0;
   float2* const P0 = lds.pair;
   float2* const P1 = P0 + Geo::NT;
+  constexpr int NX = MODE != kModeLam0 ? NCH - 1 : 0;  // channels kept beside the pairs
+  float* const X0 = lds.chan;
+  float* const X1 = X0 + NX * Geo::NT;
   float* const StD = lds.stD;
   float* const StI = lds.stI;
   float* const Res = lds.res;
@@ -213,7 +226,7 @@ __device__ __forceinline__ bool run_pass_cell(const PassDesc* gp, unsigned long 
   auto slot_base = [&](const Item& it, int kb) { return g.sign > 0 ? it.t0 - 1 - kb : Na - it.t0 - kb; };
 
   // Plane j of an item is used by the cells within distance kk - j of the tile.
-  float nx[K + 1], nd[K + 1];
+  float nx[K + 1], nd[K + 1], nxc[K + 1][NX > 0 ? NX : 1];
   // A 16-bit image's raw bits: widened where consumed, so that no load of the
   // prefetch is waited for when it is issued.
   unsigned nxr[K + 1];
@@ -224,8 +237,12 @@ __device__ __forceinline__ bool run_pass_cell(const PassDesc* gp, unsigned long 
       nx[j] = 0.0f;
       nxr[j] = 0u;
       nd[j] = 0.0f;
+#pragma unroll
+      for (int ch = 0; ch < NX; ++ch) nxc[j][ch] = 0.0f;
       if (need) {
         const int x = xof(it, j);
+#pragma unroll
+        for (int ch = 0; ch < NX; ++ch) nxc[j][ch] = gImage[(long long)(ch + 1) * g.N + x];
         if (USE_I) {
           if constexpr (FMT == kImgF32)
             nx[j] = gImage[x];
@@ -359,7 +376,7 @@ __device__ __forceinline__ bool run_pass_cell(const PassDesc* gp, unsigned long 
     const Item nxt = item_of(has_next ? n + 1 : n);
 
     // 1. This item's image and D_old.
-    float ix[K + 1], dd[K + 1];
+    float ix[K + 1], dd[K + 1], ixc[K + 1][NX > 0 ? NX : 1];
     if (SCANC) {
       __builtin_amdgcn_s_waitcnt(0);  // the global->LDS copies have landed
       __syncthreads();
@@ -386,6 +403,8 @@ __device__ __forceinline__ bool run_pass_cell(const PassDesc* gp, unsigned long 
         else
           ix[j] = widen<FMT>((uint16_t)nxr[j]);
         dd[j] = nd[j];
+#pragma unroll
+        for (int ch = 0; ch < NX; ++ch) ixc[j][ch] = nxc[j][ch];
       }
     }
     // The initialising pass reads the mask: D_old = v * M (1 * x == x otherwise).
@@ -410,6 +429,11 @@ __device__ __forceinline__ bool run_pass_cell(const PassDesc* gp, unsigned long 
     // Cells outside the volume hold +inf in both planes, so candidates through
     // them never win and the candidate loop needs no bounds checks.
     P0[tid] = make_float2(d0, ix[0]);
+#pragma unroll
+    for (int ch = 0; ch < NX; ++ch) {
+      X0[ch * Geo::NT + tid] = ixc[0][ch];
+      if (!cur.in) X1[ch * Geo::NT + tid] = 0.0f;
+    }
     if (!cur.in) P1[tid] = make_float2(__builtin_inff(), 0.0f);
     if (fail) *lds.fail = n + 1;
     step_barrier();
@@ -426,12 +450,17 @@ __device__ __forceinline__ bool run_pass_cell(const PassDesc* gp, unsigned long 
     // 3. The chunk's planes.
     float2* Pp = P0;
     float2* Pc = P1;
+    float* Xp = X0;
+    float* Xc = X1;
     unsigned long long* xout = xbuf + (size_t)(c & 1) * ntiles * (TP * TQ) + (size_t)cur.tile * (TP * TQ);
 #pragma unroll
     for (int i = 0; i < K; ++i) {
       if (i >= kk) break;
       if (cur.in && e <= kk - 1 - i) {
-        const float ixj = ix[i + 1];
+        float ixj[NX + 1];
+        ixj[0] = ix[i + 1];
+#pragma unroll
+        for (int ch = 0; ch < NX; ++ch) ixj[ch + 1] = ixc[i + 1][ch];
         float best = dd[i + 1];
         int choice = 0;
 #pragma unroll
@@ -440,7 +469,11 @@ __device__ __forceinline__ bool run_pass_cell(const PassDesc* gp, unsigned long 
           for (int dq = -1; dq <= 1; ++dq) {
             const int j = (dp + 1) * 3 + dq + 1;
             const float2 y = Pp[tid + dp * BQ + dq];
-            const float cand = y.x + cell_edge<MODE>(g, j, ixj, y.y);
+            float iy[NX + 1];
+            iy[0] = y.y;
+#pragma unroll
+            for (int ch = 0; ch < NX; ++ch) iy[ch + 1] = Xp[ch * Geo::NT + tid + dp * BQ + dq];
+            const float cand = y.x + cell_edge<MODE, NX + 1>(g, j, ixj, iy);
             if (REC) {
               if (cand < best) {
                 best = cand;
@@ -451,7 +484,9 @@ __device__ __forceinline__ bool run_pass_cell(const PassDesc* gp, unsigned long 
             }
           }
         }
-        Pc[tid] = make_float2(best, ixj);
+        Pc[tid] = make_float2(best, ixj[0]);
+#pragma unroll
+        for (int ch = 0; ch < NX; ++ch) Xc[ch * Geo::NT + tid] = ixj[ch + 1];
         if (e == 0) {
           chg |= best < dd[i + 1];
           const int x = xof(cur, i + 1);
@@ -469,6 +504,9 @@ __device__ __forceinline__ bool run_pass_cell(const PassDesc* gp, unsigned long 
       float2* t = Pp;
       Pp = Pc;
       Pc = t;
+      float* tx = Xp;
+      Xp = Xc;
+      Xc = tx;
     }
 
     // 4. Scan-contiguous results: each own cell's kk planes as one run of
@@ -497,18 +535,18 @@ __device__ __forceinline__ bool run_pass_cell(const PassDesc* gp, unsigned long 
 
 // Requested mode RMODE falls back to the general formula when the image
 // classification word rules the fast edge cost out.
-template <bool SCANC, int RMODE, bool REC, class Geo = CellGeomBase, int FMT = kImgF32>
+template <bool SCANC, int RMODE, bool REC, class Geo = CellGeomBase, int FMT = kImgF32, int NCH = 1>
 __device__ __forceinline__ bool run_pass_cell_mode(const PassDesc* gp, unsigned long long* xbuf, unsigned* words,
                                                    const unsigned* cls_word, unsigned long long limit,
                                                    const CellLds& lds, int wg, int G) {
   if (RMODE == kModeGeneral) {
     if (general_n_ok(gp->sqrt_normal, cls_word))
-      return run_pass_cell<SCANC, kModeGeneralN, REC, Geo, FMT>(gp, xbuf, words, limit, lds, wg, G);
-    return run_pass_cell<SCANC, kModeGeneral, REC, Geo, FMT>(gp, xbuf, words, limit, lds, wg, G);
+      return run_pass_cell<SCANC, kModeGeneralN, REC, Geo, FMT, NCH>(gp, xbuf, words, limit, lds, wg, G);
+    return run_pass_cell<SCANC, kModeGeneral, REC, Geo, FMT, NCH>(gp, xbuf, words, limit, lds, wg, G);
   }
   const bool fast = fast_mode_ok(RMODE, ld_relaxed(cls_word));
-  if (fast) return run_pass_cell<SCANC, RMODE, REC, Geo, FMT>(gp, xbuf, words, limit, lds, wg, G);
-  return run_pass_cell<SCANC, kModeGeneral, REC, Geo, FMT>(gp, xbuf, words, limit, lds, wg, G);
+  if (fast) return run_pass_cell<SCANC, RMODE, REC, Geo, FMT, NCH>(gp, xbuf, words, limit, lds, wg, G);
+  return run_pass_cell<SCANC, kModeGeneral, REC, Geo, FMT, NCH>(gp, xbuf, words, limit, lds, wg, G);
 }
 
 // Layout and requested mode chosen at run time (batched launches).
