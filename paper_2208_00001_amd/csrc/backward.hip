@@ -1,5 +1,6 @@
-// Backward (reverse-mode) kernels: one launch per reversed pass of one instance,
-// and the batched persistent launch over many instances (see backward_device.h).
+// Batched backward (reverse-mode) kernels: one persistent launch over many
+// instances (see backward_device.h; the single-instance reverse is in
+// bwd_split.hip).
 #include "backward_cell.h"
 #include "backward_device.h"
 #include "grid_sync.h"
@@ -9,57 +10,6 @@ namespace ggdt {
 namespace {
 
 using namespace dev;
-
-template <int NDIM, int TP, int TQ, int K, bool SCANC>
-__global__ __launch_bounds__(kThreads) void bwd_pass_kernel(BwdDesc g, unsigned* words, unsigned long long limit) {
-  extern __shared__ __align__(16) float lds[];
-  if (ld_relaxed(words + kWordAbort) != 0u) return;
-  run_bwd_pass_mode<NDIM, TP, TQ, K, SCANC>(&g, g.xbuf, words, words + kWordClass, limit, lds,
-                                            xcd_remap(blockIdx.x, gridDim.x), gridDim.x);
-}
-
-// Single-channel 3D reversed passes on 16 x 16 tiles with K = 8: one thread per box cell.
-__global__ __launch_bounds__(kCellThreads) void bwd_pass_cell_kernel(BwdDesc g, unsigned* words,
-                                                                     unsigned long long limit) {
-  __shared__ float lds[(kBwdCellLdsBytes + 3) / 4];
-  if (ld_relaxed(words + kWordAbort) != 0u) return;
-  run_bwd_pass_cell_mode(&g, g.xbuf, words, words + kWordClass, limit, lds, xcd_remap(blockIdx.x, gridDim.x),
-                         gridDim.x);
-}
-
-bool use_bwd_cell(const BwdDesc& d, int ndim) {
-  return ndim == 3 && d.C == 1 && d.K == kCellK && d.TP == kCellTP && d.TQ == kCellTQ;
-}
-
-using BwdKernel = void (*)(BwdDesc, unsigned*, unsigned long long);
-
-template <int NDIM, int TP, int TQ, int K>
-BwdKernel pick_bwd(bool scanc) {
-  return scanc ? bwd_pass_kernel<NDIM, TP, TQ, K, true> : bwd_pass_kernel<NDIM, TP, TQ, K, false>;
-}
-
-BwdKernel select_bwd(const BwdDesc& d, int ndim) {
-  const bool scanc = d.sa == 1;
-  if (ndim == 3) {
-    if (d.K == 4) return pick_bwd<3, kTP3, kTQ3, 4>(scanc);
-    if (d.K == 2) return pick_bwd<3, kTP3, kTQ3, 2>(scanc);
-  } else {
-    if (d.K == 16) return pick_bwd<2, 1, kTQ2, 16>(scanc);
-    if (d.K == 8) return pick_bwd<2, 1, kTQ2, 8>(scanc);
-  }
-  return nullptr;
-}
-
-size_t bwd_lds(int ndim, int K, int C, bool scanc) {
-  if (ndim == 3) {
-    if (K == 4) return scanc ? BLayout<3, kTP3, kTQ3, 4, true>::bytes(C) : BLayout<3, kTP3, kTQ3, 4, false>::bytes(C);
-    if (K == 2) return scanc ? BLayout<3, kTP3, kTQ3, 2, true>::bytes(C) : BLayout<3, kTP3, kTQ3, 2, false>::bytes(C);
-  } else {
-    if (K == 16) return scanc ? BLayout<2, 1, kTQ2, 16, true>::bytes(C) : BLayout<2, 1, kTQ2, 16, false>::bytes(C);
-    if (K == 8) return scanc ? BLayout<2, 1, kTQ2, 8, true>::bytes(C) : BLayout<2, 1, kTQ2, 8, false>::bytes(C);
-  }
-  return 0;
-}
 
 int capacity_of(const void* fn, size_t lds, int threads = kThreads) {
   int dev = 0, cus = 0, per_cu = 0;
@@ -162,39 +112,6 @@ __global__ __launch_bounds__(kCellThreads) void batched_bwd_kernel(const BatchIn
 }
 
 }  // namespace
-
-int bwd_chunk_for(int ndim, int C, bool scan_contiguous) {
-  if (ndim == 3 && C == 1) return kCellK;  // thread-per-cell reverse pass
-  const int ks3[2] = {4, 2}, ks2[2] = {16, 8};
-  for (int i = 0; i < 2; ++i) {
-    const int K = ndim == 3 ? ks3[i] : ks2[i];
-    if (bwd_lds(ndim, K, C, scan_contiguous) <= kMaxLdsBytes) return K;
-  }
-  return 0;
-}
-
-hipError_t launch_bwd_pass(const BwdDesc& d, int ndim, unsigned* words, unsigned long long spin_limit,
-                           hipStream_t stream) {
-  if (use_bwd_cell(d, ndim)) {
-    static int cap_cell = 0;
-    if (cap_cell <= 0) cap_cell = capacity_of((const void*)bwd_pass_cell_kernel, 0, kCellThreads);
-    if (cap_cell <= 0) return hipErrorInvalidConfiguration;
-    const int ntiles = d.ntp * d.ntq;
-    const int grid = ntiles < cap_cell ? ntiles : cap_cell;
-    hipLaunchKernelGGL(bwd_pass_cell_kernel, dim3(grid), dim3(kCellThreads), 0, stream, d, words, spin_limit);
-    return hipGetLastError();
-  }
-  BwdKernel fn = select_bwd(d, ndim);
-  if (!fn) return hipErrorInvalidConfiguration;
-  const size_t lds = bwd_lds(ndim, d.K, d.C, d.sa == 1);
-  if (lds == 0 || lds > kMaxLdsBytes) return hipErrorInvalidConfiguration;
-  const int cap = capacity_of((const void*)fn, lds);
-  if (cap <= 0) return hipErrorInvalidConfiguration;
-  const int ntiles = d.ntp * d.ntq;
-  const int grid = ntiles < cap ? ntiles : cap;
-  hipLaunchKernelGGL(fn, dim3(grid), dim3(kThreads), lds, stream, d, words, spin_limit);
-  return hipGetLastError();
-}
 
 // c2 / c3: the largest channel count of the batch's 2D / 3D instances (0: none).
 size_t batched_bwd_lds_bytes(int c2, int c3) {

@@ -189,10 +189,22 @@ hipError_t launch_batched(int kclass, bool rec, const BatchInst* insts, int nins
                           unsigned char* ws, int grid, size_t lds, unsigned long long spin_limit, hipStream_t stream);
 hipError_t launch_batched_classify(const BatchInst* insts, int ninst, unsigned char* ws, hipStream_t stream);
 
-// Chunk length of the backward kernels for a geometry (0 if none fits).
-int bwd_chunk_for(int ndim, int C, bool scan_contiguous);
-hipError_t launch_bwd_pass(const BwdDesc& d, int ndim, unsigned* words, unsigned long long spin_limit,
+// Second launch of a single-instance reversed pass (bwd_split.hip): a is the
+// scan's output (abar before zeroing), out the next pass's abar_in, gI the
+// image gradient.
+struct EdgeDesc {
+  const float* a;
+  float* out;
+  float* gI;
+  int d1, d2;   // sizes of the array's last two axes (2D: d1 unused)
+  int axis;     // the pass's scan axis
+  int first;    // gI is not read (zero so far)
+  int last;     // out = v * abar
+  float v;
+};
+hipError_t launch_bwd_scan(const BwdDesc& d, int ndim, unsigned* words, unsigned long long spin_limit,
                            hipStream_t stream);
+hipError_t launch_bwd_edges(const BwdDesc& g, int ndim, const EdgeDesc& s, const unsigned* words, hipStream_t stream);
 size_t batched_bwd_lds_bytes(int c2, int c3);
 // Batched reverse kernel class: 0 when every instance is a single-channel volume
 // (thread-per-cell reverse pass), else 1 (tile reverse passes).

@@ -1,0 +1,89 @@
+"""Tile geometries of the 3D passes and their reverse, against the oracle bit
+for bit: planes at the edges of each tile size's range (8 x 8 while at most 256
+tiles cover the plane, then 8 x 16, then 16 x 16), ragged tiles, chunk
+remainders, one to three channels, and planes with more tiles than workgroups.
+The kernels run the oracle's FP32 operations in its order, so the tolerance is
+zero."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import DEV, to_dev, to_host
+from paper_2208_00001_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+# axis 0 scans a plane of H x W: 256 tiles of 8 x 8; one row more; 256 of 8 x 16; one row more
+PLANES = [(9, 128, 128), (10, 129, 127), (17, 128, 256), (9, 136, 257)]
+
+
+def same(got, ref, what):
+    got, ref = np.asarray(got), np.asarray(ref).reshape(got.shape)
+    assert np.array_equal(got, ref), f"{what}: {int((got != ref).sum())} values differ"
+
+
+@pytest.mark.parametrize("shape", PLANES, ids=str)
+@pytest.mark.parametrize("C,lam", [(1, 0.5), (1, 1.0), (1, 0.0), (2, 0.5), (3, 1.0), (2, 0.0)])
+def test_forward_records_and_backward(shape, C, lam):
+    from paper_2208_00001_amd import binding as B
+    c = synth.small_case(shape, C=C, seed=40 + C, lam=lam, iterations=1, soft=True, v=10.0)
+    W = np.random.default_rng(41).standard_normal(shape).astype(np.float32)
+    args = (c["spacing"], c["v"], c["lam"], 1)
+    ref, rrec = oracle.ggdt(c["image"], c["mask"], *args, "f32", records=True)
+    rgi, rgm = oracle.backward(c["image"], rrec, W, *args, "f32")
+    img, m = to_dev(c["image"]), to_dev(c["mask"])
+    print(f"case {c['name']} lam={lam}", flush=True)
+    for minimal in (False, True):  # last axis on scan-major copies, and in place
+        ws = B.new_workspace(shape, C, DEV, minimal=minimal)
+        same(to_host(B.ggdt3d(img, m, *args, workspace=ws, check=True)), ref, "forward")
+        out, rec = B.ggdt_forward_rec(img, m, *args, workspace=ws, check=True)
+        same(to_host(out), ref, "forward with records")
+        same(to_host(rec), rrec, "records")
+    gi, gm = B.ggdt_backward(img, rec, to_dev(W), *args, check=True)
+    same(to_host(gm), rgm, "dL/dM")
+    same(to_host(gi), rgi, "dL/dI")
+
+
+@pytest.mark.parametrize("C", [1, 2])
+def test_more_tiles_than_workgroups(C):
+    from paper_2208_00001_amd import binding as B
+    shape = (4, 620, 500)  # axis 0: 39 x 32 tiles of 16 x 16
+    c = synth.small_case(shape, C=C, seed=50, lam=0.6, iterations=1, soft=True, v=10.0)
+    W = np.random.default_rng(51).standard_normal(shape).astype(np.float32)
+    args = (c["spacing"], c["v"], c["lam"], 1)
+    ref, rrec = oracle.ggdt(c["image"], c["mask"], *args, "f32", records=True)
+    rgi, rgm = oracle.backward(c["image"], rrec, W, *args, "f32")
+    img, m = to_dev(c["image"]), to_dev(c["mask"])
+    out, rec = B.ggdt_forward_rec(img, m, *args, check=True)
+    same(to_host(out), ref, "forward")
+    gi, gm = B.ggdt_backward(img, rec, to_dev(W), *args, check=True)
+    same(to_host(gm), rgm, "dL/dM")
+    same(to_host(gi), rgi, "dL/dI")
+
+
+@pytest.mark.parametrize("C,lam,scale", [(2, 0.0, 2.0 ** 61), (2, 0.5, 2.0 ** 61), (3, 1.0, 2.0 ** -30)])
+def test_multichannel_fallback_cost(C, lam, scale):
+    """Huge or small image values: the general cost with the full root."""
+    from paper_2208_00001_amd import binding as B
+    shape = (11, 30, 21)
+    c = synth.small_case(shape, C=C, seed=60, lam=lam, iterations=2)
+    image = (c["image"] * np.float32(scale)).astype(np.float32)
+    ref = oracle.ggdt(image, c["mask"], c["spacing"], c["v"], c["lam"], 2, "f32")
+    got = B.ggdt3d(to_dev(image), to_dev(c["mask"]), c["spacing"], c["v"], c["lam"], 2, check=True)
+    same(to_host(got), ref, "forward")
+
+
+@pytest.mark.parametrize("shape,C", [((17, 33), 1), ((18, 32), 2), ((34, 31), 3), ((70, 65), 4), ((1, 40), 1),
+                                     ((40, 1), 3), ((2, 2), 8)], ids=str)
+@pytest.mark.parametrize("lam", [0.0, 0.6, 1.0])
+def test_image_backward(shape, C, lam):
+    """The reverse of 2D passes at the edges of its 32-cell tiles and 16-row chunks."""
+    from paper_2208_00001_amd import binding as B
+    c = synth.small_case(shape, C=C, seed=70 + C, lam=lam, iterations=2, soft=True, v=10.0)
+    W = np.random.default_rng(71).standard_normal(shape).astype(np.float32)
+    args = (c["spacing"], c["v"], c["lam"], 2)
+    _, rrec = oracle.ggdt(c["image"], c["mask"], *args, "f32", records=True)
+    rgi, rgm = oracle.backward(c["image"], rrec, W, *args, "f32")
+    gi, gm = B.ggdt_backward(to_dev(c["image"]), to_dev(rrec), to_dev(W), *args, check=True)
+    same(to_host(gm), rgm, "dL/dM")
+    same(to_host(gi), rgi, "dL/dI")
