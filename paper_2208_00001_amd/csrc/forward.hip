@@ -4,6 +4,7 @@
 #include "cell_kernels.h"
 #include "pass_device.h"
 #include "pass_row.h"
+#include "pass_team.h"
 
 namespace ggdt {
 namespace {
@@ -28,6 +29,18 @@ __global__ __launch_bounds__(kRowLanes) void pass_row_kernel(PassDesc g, unsigne
                                           xcd_remap(blockIdx.x, gridDim.x), gridDim.x);
 }
 
+// The same with producer waves for the edge costs (lambda above 0).
+template <int RMODE, int NCH, bool REC, int FMT = kImgF32>
+__global__ __launch_bounds__(kTeamThreads) void pass_team_kernel(PassDesc g, unsigned* words,
+                                                                 unsigned long long limit) {
+  __shared__ float costs[2 * kTeamChunk];
+  __shared__ int fail;
+  if (ld_relaxed(words + kWordAbort) != 0u) return;
+  if (g.converge && ld_relaxed(words + kWordDone) != 0u) return;  // an earlier iteration changed nothing
+  run_pass_team_mode<RMODE, NCH, REC, FMT>(&g, g.xbuf, words, words + kWordClass, limit, costs, &fail,
+                                           xcd_remap(blockIdx.x, gridDim.x), gridDim.x);
+}
+
 bool use_row_path(const PassDesc& d, int ndim) {
   return ndim == 2 && d.TP == 1 && d.TQ == kRowTQ && d.K == kRowK && d.C >= 1 && d.C <= kRowMaxC && d.ntp == 1;
 }
@@ -35,8 +48,8 @@ bool use_row_path(const PassDesc& d, int ndim) {
 template <int NCH, bool REC, int FMT = kImgF32>
 PassKernel select_row_mode(int mode) {
   if (mode == kModeLam0) return pass_row_kernel<kModeLam0, NCH, REC, FMT>;
-  if (NCH == 1 && mode == kModeLam1C1) return pass_row_kernel<kModeLam1C1, 1, REC, FMT>;
-  return pass_row_kernel<kModeGeneral, NCH, REC, FMT>;
+  if (NCH == 1 && mode == kModeLam1C1) return pass_team_kernel<kModeLam1C1, 1, REC, FMT>;
+  return pass_team_kernel<kModeGeneral, NCH, REC, FMT>;
 }
 
 template <bool REC, int FMT = kImgF32>
@@ -205,10 +218,11 @@ hipError_t launch_pass(const PassDesc& d, int ndim, unsigned* words, unsigned lo
   if (use_row_path(d, ndim)) {
     PassKernel fn = select_row_kernel(d);
     if (!fn) return hipErrorInvalidConfiguration;
-    const int cap = capacity_for(fn, 0, kRowLanes);
+    const int threads = d.mode == kModeLam0 ? kRowLanes : kTeamThreads;
+    const int cap = capacity_for(fn, 0, threads);
     if (cap <= 0) return hipErrorInvalidConfiguration;
     const int grid = d.ntq < cap ? d.ntq : cap;
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(kRowLanes), 0, stream, d, words, spin_limit);
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(threads), 0, stream, d, words, spin_limit);
     return hipGetLastError();
   }
   if (ndim == 3 && d.K == kCellK && use_cell_path(d)) {

@@ -1,0 +1,237 @@
+// Directional pass of a 2D image by a team of four wavefronts per tile.
+//
+// A row's edge costs depend on the image alone, not on the distances of the row
+// before, but a lone wave runs them inside the serial chain of rows: at
+// lambda in (0, 1) with three channels 50 of a row step's 75 instructions, at
+// one instruction per four cycles.  Here three producer waves compute the costs
+// of the next chunk's rows into LDS, each on a SIMD of its own, while the chain
+// wave advances the current chunk: a step of it is three additions and minima,
+// whatever the channel count.  Tiles, chunks, exchange words and the lanes'
+// cells are those of the row pass (pass_row.h).
+#pragma once
+
+#include "pass_cell.h"
+#include "pass_row.h"
+
+namespace ggdt {
+namespace dev {
+
+constexpr int kTeamThreads = 4 * kRowLanes;
+// costs of one chunk: [row][offset][lane]
+constexpr int kTeamChunk = kRowK * 3 * kRowLanes;
+
+// One 2D pass by workgroup `wg` of G (kTeamThreads threads).  `costs`: two
+// chunks in LDS; `failw`: one LDS word.  False if a bounded wait gave up.
+template <int MODE, int NCH, bool REC, int FMT>
+__device__ __forceinline__ bool run_pass_team(const PassDesc* gp, unsigned long long* xbuf, unsigned* words,
+                                              unsigned long long limit, float* costs, int* failw, int wg, int G) {
+  static_assert(MODE != kModeLam0, "lambda 0 has no costs to produce");
+  constexpr int K = kRowK, TQ = kRowTQ;
+  const PassDesc g = *gp;
+  const auto gImage = image_of<FMT>(g.image);
+  const gmem<const float> gMask = to_gmem(g.mask);
+  const gmem<float> gD = to_gmem(g.D);
+  const gmem<uint8_t> gRec = to_gmem(g.rec);
+  const int lane = threadIdx.x & (kRowLanes - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kRowLanes);
+  const int e = max(max(K - lane, lane - (K + TQ - 1)), 0);
+  const int own = lane - K;
+  const int ntiles = g.ntq;
+  if (wg >= ntiles) return true;
+  const int Na = g.Na, Nq = g.Nq;
+  const long long cstride = g.N;
+  if (threadIdx.x == 0) *failw = 0;  // read only after a barrier
+
+  if (wave == 0 && (g.init || REC)) {  // first row in scan order
+    const int kf = g.sign > 0 ? 0 : Na - 1;
+    for (int tile = wg; tile < ntiles; tile += G) {
+      const int q = tile * TQ + own;
+      if (e == 0 && q < Nq) {
+        const int x = kf * g.sa + q * g.sq;
+        if (g.init) gD[x] = g.v * gMask[x];
+        if (REC && g.rec) gRec[x] = 0;
+      }
+    }
+  }
+
+  const gmem<const float> dsrc0 = g.init ? gMask : (gmem<const float>)gD;
+  const float vscale = g.init ? g.v : 1.0f;
+  const int nmine = (ntiles - wg + G - 1) / G;
+  const int nitems = g.nchunk * nmine;
+  struct Item {
+    int c, tile, t0, kk, q, xq;
+    bool in;
+  };
+  auto item_of = [&](int n) {
+    Item it;
+    it.c = n / nmine;
+    it.tile = wg + (n - it.c * nmine) * G;
+    it.t0 = 1 + it.c * K;
+    it.kk = min(K, Na - it.t0);
+    it.q = it.tile * TQ - K + lane;
+    it.in = it.q >= 0 && it.q < Nq;
+    it.xq = it.in ? it.q * g.sq : 0;
+    return it;
+  };
+  auto xof = [&](const Item& it, int j) {
+    const int t = it.t0 - 1 + j;
+    return (g.sign > 0 ? t : Na - 1 - t) * g.sa + it.xq;
+  };
+  const int rstep = g.sign * g.sa;
+
+  if (wave != 0) {
+    // Producer: rows r0 .. r0 + NR - 1 of every chunk (the last producer's rows
+    // past the chunk are not stored), from image rows r0 .. r0 + NR.
+    constexpr int NR = (K + 2) / 3;
+    const int r0 = (wave - 1) * NR;
+    using T = typename ImgElem<FMT>::T;
+    T nx[NR + 1][NCH];
+    // Branch-free loads at clamped, in-bounds addresses: a row past the chunk or
+    // a lane outside the image gives costs that no cell uses.
+    auto fetch = [&](const Item& it) {
+      const int x0 = xof(it, 0);
+#pragma unroll
+      for (int j = 0; j <= NR; ++j) {
+        int x = it.in ? x0 + min(r0 + j, it.kk) * rstep : 0;
+        __asm__ volatile("" : "+v"(x));  // keeps the clamp from becoming a branch per row
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) nx[j][c] = gImage[c * cstride + x];
+      }
+    };
+    if (nitems > 0) fetch(item_of(0));
+    for (int n = 0; n <= nitems; ++n) {
+      if (n < nitems) {
+        float ix[NR + 1][NCH];
+#pragma unroll
+        for (int j = 0; j <= NR; ++j)
+#pragma unroll
+          for (int c = 0; c < NCH; ++c) ix[j][c] = widen<FMT>(nx[j][c]);
+        if (n + 1 < nitems) fetch(item_of(n + 1));
+        float* out = costs + (n & 1) * kTeamChunk + r0 * 3 * kRowLanes + lane;
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+          float iy[3][NCH];
+#pragma unroll
+          for (int c = 0; c < NCH; ++c) {
+            iy[0][c] = from_left(ix[i][c]);
+            iy[1][c] = ix[i][c];
+            iy[2][c] = from_right(ix[i][c]);
+          }
+#pragma unroll
+          for (int j = 0; j < 3; ++j) {
+            const float w = row_edge<MODE, NCH>(g, j, ix[i + 1], iy[j]);
+            if (r0 + i < K) out[(i * 3 + j) * kRowLanes] = w;
+          }
+        }
+      }
+      step_barrier();
+      if (*failw) return false;
+    }
+    return true;
+  }
+
+  // Chain wave: item n - 1 in phase n.
+  float nd[K + 1];
+  auto fetch = [&](const Item& it) {
+    const int x0 = xof(it, 0);
+    const int last = it.in ? it.kk - e : -1;  // the lane needs rows 0 .. last
+#pragma unroll
+    for (int j = 0; j <= K; ++j) {
+      int x = j <= last ? x0 + j * rstep : 0;
+      __asm__ volatile("" : "+v"(x));
+      nd[j] = dsrc0[x];
+    }
+  };
+  int chg = 0;  // an own cell was lowered (convergence mode)
+  Item cur = item_of(0);
+  if (nitems > 0) fetch(cur);
+  step_barrier();
+  for (int n = 0; n < nitems; ++n) {
+    const int c = cur.c, kk = cur.kk;
+    const unsigned epoch_in = g.epoch_base + (unsigned)c;  // published by chunk c - 1
+    const bool has_next = n + 1 < nitems;
+    const Item nxt = item_of(has_next ? n + 1 : n);
+    float dd[K + 1];
+#pragma unroll
+    for (int j = 0; j <= K; ++j) dd[j] = nd[j] * vscale;  // the initialising pass reads the mask: D_old = v * M
+    float dcur = __builtin_inff();
+    int fail = 0;
+    if (cur.in && e <= kk) {
+      if (c == 0)
+        dcur = dd[0];
+      else  // the owner's slot of cell q is q itself: tile q / TQ, slot q % TQ
+        dcur = wait_word(xbuf + (size_t)((c - 1) & 1) * ntiles * TQ + cur.q, epoch_in, words, limit, &fail);
+    }
+    if (__any(fail)) *failw = 1;
+    if (has_next) fetch(nxt);
+    const float* wc = costs + (n & 1) * kTeamChunk + lane;
+    float res[K];
+    int rch[K];
+    auto step = [&](int i) {
+      const float dy[3] = {from_left(dcur), dcur, from_right(dcur)};
+      float best = dd[i + 1];
+      int choice = 0;
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        const float cand = dy[j] + wc[(i * 3 + j) * kRowLanes];
+        if (REC) {
+          choice = cand < best ? 1 + j : choice;
+          best = cand < best ? cand : best;
+        } else {
+          best = fminf(best, cand);
+        }
+      }
+      res[i] = best;
+      rch[i] = choice;
+      dcur = cur.in ? best : __builtin_inff();
+    };
+    if (kk == K) {
+#pragma unroll
+      for (int i = 0; i < K; ++i) step(i);
+    } else {
+#pragma unroll
+      for (int i = 0; i < K; ++i)
+        if (i < kk) step(i);
+    }
+    // The exchange word of the chunk's last row first (the neighbours wait for
+    // it), then the rows.
+    if (cur.in && e == 0 && !fail) {
+      unsigned long long* xout = xbuf + (size_t)(c & 1) * ntiles * TQ + (size_t)cur.tile * TQ;
+      st64_relaxed(xout + own, ((unsigned long long)(epoch_in + 1u) << 32) | __float_as_uint(dcur));
+#pragma unroll
+      for (int i = 0; i < K; ++i) {
+        if (i < kk) {
+          const int x = xof(cur, i + 1);
+          chg |= res[i] < dd[i + 1];
+          gD[x] = res[i];
+          if (REC && g.rec) gRec[x] = (uint8_t)rch[i];
+        }
+      }
+    }
+    step_barrier();
+    if (*failw) return false;
+    cur = nxt;
+  }
+  if (g.converge && __any(chg) && lane == 0)
+    __hip_atomic_store(words + kWordChanged, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return true;
+}
+
+// Requested mode RMODE falls back to the general formula when the image
+// classification word rules the fast edge cost out.
+template <int RMODE, int NCH, bool REC, int FMT>
+__device__ __forceinline__ bool run_pass_team_mode(const PassDesc* gp, unsigned long long* xbuf, unsigned* words,
+                                                   const unsigned* cls_word, unsigned long long limit, float* costs,
+                                                   int* failw, int wg, int G) {
+  if (RMODE == kModeGeneral) {
+    if (general_n_ok(gp->sqrt_normal, cls_word))
+      return run_pass_team<kModeGeneralN, NCH, REC, FMT>(gp, xbuf, words, limit, costs, failw, wg, G);
+    return run_pass_team<kModeGeneral, NCH, REC, FMT>(gp, xbuf, words, limit, costs, failw, wg, G);
+  }
+  if (fast_mode_ok(RMODE, ld_relaxed(cls_word)))
+    return run_pass_team<RMODE, NCH, REC, FMT>(gp, xbuf, words, limit, costs, failw, wg, G);
+  return run_pass_team<kModeGeneral, NCH, REC, FMT>(gp, xbuf, words, limit, costs, failw, wg, G);
+}
+
+}  // namespace dev
+}  // namespace ggdt
