@@ -8,8 +8,11 @@
 // the co-resident capacity, which the bounded waits require.
 #include "pass_cell.h"
 #include "pass_device.h"
+#include "pass_team.h"
 #include "grid_sync.h"
 #include "layout.h"
+
+#include <type_traits>
 
 namespace ggdt {
 namespace {
@@ -23,9 +26,9 @@ __device__ __forceinline__ bool instance_barrier(unsigned* counter, unsigned tar
   return counter_barrier<unsigned>(counter, target, words, limit);
 }
 
-// Batched workgroups have kBatchThreads threads: single-channel 3D instances
-// (class 0, K = 8) run the thread-per-cell pass, the others the tile pass with
-// that many threads.
+// Batched workgroups have kBatchThreads threads: the instances of single-channel
+// batches run the thread-per-cell pass (3D) and four teams (2D), those of
+// multi-channel batches the tile pass with that many threads.
 constexpr int kBatchThreads = kCellThreads;
 
 template <int NDIM, int TP, int TQ, int K, bool REC>
@@ -45,8 +48,9 @@ __device__ __forceinline__ bool run_pass_rt(const PassDesc* gp, unsigned long lo
 }
 
 // A layout change of one instance (PassDesc::op) by its G workgroups;
-// PassDesc::K: tiles per round the launch's LDS holds (4, else 1).
-__device__ __forceinline__ bool run_layout_op(const PassDesc* gp, unsigned* words, float* lds, int wg, int G) {
+// PassDesc::K: tiles per round the launch's LDS holds (4, else 1).  Out of
+// line: its registers would make the passes spill.
+__device__ __attribute__((noinline)) bool run_layout_op(const PassDesc* gp, unsigned* words, float* lds, int wg, int G) {
   const PassDesc g = resolve_offsets(*gp, words);
   const TransposeShape sh = transpose_shape(g.op == kOpToScanMajor, g.Np, g.Nq, g.Na);
   if (g.esz == 1) {  // records (byte volumes)
@@ -63,11 +67,29 @@ __device__ __forceinline__ bool run_layout_op(const PassDesc* gp, unsigned* word
   return true;
 }
 
-// CT: tile side of the thread-per-cell pass for 3D instances (0: the tile pass).
-template <int K3, int K2, bool REC, int CT>
+// A 2D pass of a single-channel image: the workgroup's 16 waves are four teams.
+constexpr int kBatchTeams = kBatchThreads / kTeamThreads;
+static_assert(kBatchTeams == kBatchTeamsPerWg, "the plan's workgroup split counts a workgroup's teams");
+template <int K, bool REC>
+__device__ __forceinline__ bool run_pass_teams(const PassDesc* gp, unsigned long long* xbuf, unsigned* words,
+                                               const unsigned* cls, int mode, unsigned long long limit, float* lds,
+                                               int wg, int G) {
+  constexpr int NT = kBatchTeams;
+  int* failw = reinterpret_cast<int*>(lds + NT * 2 * team_chunk(K));
+  if (mode == kModeLam0)
+    return run_pass_team_mode<kModeLam0, 1, REC, kImgF32, K, NT>(gp, xbuf, words, cls, limit, lds, failw, wg, G);
+  if (mode == kModeLam1C1)
+    return run_pass_team_mode<kModeLam1C1, 1, REC, kImgF32, K, NT>(gp, xbuf, words, cls, limit, lds, failw, wg, G);
+  return run_pass_team_mode<kModeGeneral, 1, REC, kImgF32, K, NT>(gp, xbuf, words, cls, limit, lds, failw, wg, G);
+}
+
+// Geo: tile geometry of the thread-per-cell pass for 3D instances, whose 2D
+// instances run on teams (void: the tile passes).
+template <int K3, int K2, bool REC, class Geo>
 __global__ __launch_bounds__(kBatchThreads) void batched_kernel(const BatchInst* __restrict__ insts, int ninst,
                                                            const PassDesc* __restrict__ passes, unsigned char* ws,
                                                            unsigned long long limit) {
+  constexpr bool CELL = !std::is_void<Geo>::value;
   extern __shared__ __align__(16) float lds[];
   unsigned* words = reinterpret_cast<unsigned*>(ws);
   if (ld_relaxed(words + kWordAbort) != 0u) return;
@@ -90,10 +112,12 @@ __global__ __launch_bounds__(kBatchThreads) void batched_kernel(const BatchInst*
     if (gp->op != kOpPass) {
       ok = run_layout_op(gp, words, lds, wg, in.nwg);
     } else if (in.ndim == 3) {
-      if constexpr (CT != 0)
-        ok = run_pass_cell_rt<REC, CellGeom<CT, CT, K3>>(gp, xbuf, words, cls, in.mode, limit, carve_cell_lds(lds), wg, in.nwg);
+      if constexpr (CELL)
+        ok = run_pass_cell_rt<REC, Geo>(gp, xbuf, words, cls, in.mode, limit, carve_cell_lds(lds), wg, in.nwg);
       else
         ok = run_pass_rt<3, kTP3, kTQ3, K3, REC>(gp, xbuf, words, cls, in.mode, limit, lds, wg, in.nwg);
+    } else if constexpr (CELL) {
+      ok = run_pass_teams<K2, REC>(gp, xbuf, words, cls, in.mode, limit, lds, wg, in.nwg);
     } else {
       ok = run_pass_rt<2, 1, kTQ2, K2, REC>(gp, xbuf, words, cls, in.mode, limit, lds, wg, in.nwg);
     }
@@ -127,32 +151,28 @@ __global__ __launch_bounds__(256) void batched_classify_kernel(const BatchInst* 
 
 using BatchedKernel = void (*)(const BatchInst*, int, const PassDesc*, unsigned char*, unsigned long long);
 
-static_assert(kBatchTile3[0] == kCellTP && kBatchK3[0] == kCellK && kBatchTile3[2] == kCellWideTP &&
-                  kBatchK3[2] == kCellWideK,
-              "batched classes 0 and 2 run the thread-per-cell pass geometries");
-
 template <int C>
 BatchedKernel pick_class(bool rec) {
-  constexpr int CT = C == 1 ? 0 : kBatchTile3[C];
-  return rec ? batched_kernel<kBatchK3[C], kBatchK2[C], true, CT> : batched_kernel<kBatchK3[C], kBatchK2[C], false, CT>;
+  using Geo = std::conditional_t<C == 1, void, CellGeomPadded<CellGeom<kBatchTP3[C], kBatchTQ3[C], kBatchK3[C]>>>;
+  return rec ? batched_kernel<kBatchK3[C], kBatchK2[C], true, Geo> : batched_kernel<kBatchK3[C], kBatchK2[C], false, Geo>;
 }
 
 BatchedKernel pick(int kclass, bool rec) {
-  if (kclass == 0) return pick_class<0>(rec);
-  if (kclass == 2) return pick_class<2>(rec);
-  return pick_class<1>(rec);
+  switch (kclass) {
+    case 0: return pick_class<0>(rec);
+    case 2: return pick_class<2>(rec);
+    case 3: return pick_class<3>(rec);
+    case 4: return pick_class<4>(rec);
+    default: return pick_class<1>(rec);
+  }
 }
 
-template <int K3, int K2, bool CELL>
+template <int K3, int K2>
 size_t lds_for(int C, bool has2d, bool has3d) {
   size_t b = 0;
   if (has3d) {
-    if (CELL) {
-      b = max(b, kCellLdsBytes);
-    } else {
-      b = max(b, Layout<3, kTP3, kTQ3, K3, true>::bytes(C));
-      b = max(b, Layout<3, kTP3, kTQ3, K3, false>::bytes(C));
-    }
+    b = max(b, Layout<3, kTP3, kTQ3, K3, true>::bytes(C));
+    b = max(b, Layout<3, kTP3, kTQ3, K3, false>::bytes(C));
   }
   if (has2d) {
     b = max(b, Layout<2, 1, kTQ2, K2, true>::bytes(C));
@@ -161,12 +181,18 @@ size_t lds_for(int C, bool has2d, bool has3d) {
   return b;
 }
 
+// Single-channel batches: the pairs of the thread-per-cell pass, the teams'
+// costs, and four tiles of the layout changes.
+constexpr size_t kTeamBatchLds = sizeof(float) * (kBatchTeams * 2 * team_chunk(kBatchK2[0]) + 1);
+constexpr size_t kLayoutLds = sizeof(float) * 4 * kTrTileElems;
+constexpr size_t kCellBatchLds = kTeamBatchLds > kLayoutLds ? kTeamBatchLds : kLayoutLds;
+static_assert(kCellBatchLds >= kCellLdsBytes && kBatchK2[0] == kBatchK2[2], "LDS of a single-channel batch");
+
 }  // namespace
 
 size_t batched_lds_bytes(int kclass, int C, bool has2d, bool has3d) {
-  if (kclass == 0) return lds_for<kBatchK3[0], kBatchK2[0], true>(C, has2d, has3d);
-  if (kclass == 2) return lds_for<kBatchK3[2], kBatchK2[2], true>(C, has2d, has3d);
-  return lds_for<kBatchK3[1], kBatchK2[1], false>(C, has2d, has3d);
+  if (kclass != 1) return kCellBatchLds;
+  return lds_for<kBatchK3[1], kBatchK2[1]>(C, has2d, has3d);
 }
 
 int batched_capacity(int kclass, bool rec, size_t lds) {

@@ -41,6 +41,13 @@ namespace {
 constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
+// Work of one workgroup at a time in a pass: a tile, or the tiles of an image
+// that a workgroup's teams walk side by side.
+int wg_tiles(const PassDesc& d) {
+  if (d.TP == 1 && d.TQ != kTQ2) return (d.ntq + kBatchTeamsPerWg - 1) / kBatchTeamsPerWg;
+  return d.ntp * d.ntq;
+}
+
 // Cost of an instance with w workgroups, in units of one strided 3D plane
 // step of one tile: over the passes, planes times the tiles each workgroup
 // walks (ceil(tiles / w)) times the step's weight, plus a per-chunk exchange
@@ -48,7 +55,7 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 // per-pass durations in a 64-instance batch on MI355X (1.26 us per strided 3D
 // plane step of a tile and 0.23 us per chunk; 2.45 us per step when the scan
 // axis is the contiguous one; 0.53 us per 2D row step and 3.5 us per chunk;
-// 3.9 us per round of 4 layout tiles).
+// 3.9 us per round of 4 layout tiles; teams 3.2 us per chunk of 16 rows).
 double instance_cost(const std::vector<PassDesc>& ps, int w) {
   double c = 0.0;
   for (const PassDesc& d : ps) {
@@ -57,8 +64,11 @@ double instance_cost(const std::vector<PassDesc>& ps, int w) {
       c += 3.1 * ceil(tiles / ((double)w * (d.K > 0 ? d.K : 1)));
       continue;
     }
-    const int tiles = d.ntp * d.ntq;
-    const int per = (tiles + w - 1) / w;
+    const int per = (wg_tiles(d) + w - 1) / w;
+    if (d.TP == 1 && d.TQ != kTQ2) {  // teams
+      c += 2.6 * d.nchunk * per;
+      continue;
+    }
     const bool two_d = d.TP == 1;
     const double step = two_d ? 0.42 : (d.sa == 1 ? 1.9 : 1.0);
     c += step * (double)(d.Na - 1) * per + (two_d ? 2.8 : 0.19) * d.nchunk;
@@ -68,7 +78,7 @@ double instance_cost(const std::vector<PassDesc>& ps, int w) {
 
 int max_tiles_of(const std::vector<PassDesc>& ps) {
   int m = 1;
-  for (const PassDesc& d : ps) m = d.ntp * d.ntq > m ? d.ntp * d.ntq : m;
+  for (const PassDesc& d : ps) m = wg_tiles(d) > m ? wg_tiles(d) : m;
   return m;
 }
 
@@ -85,6 +95,38 @@ size_t max_cells_of(const std::vector<PassDesc>& ps) {
     m = bwd > m ? bwd : m;
   }
   return m;
+}
+
+// Class of a single-channel batch without a tuning, from its number of
+// workgroups' worth of tiles against the 256 CUs: the smallest volume tile that
+// leaves every tile a CU of its own (as cell_tile does for one volume), and
+// 24 x 24 tiles beyond 1.75 tiles of 16 x 16 per CU, where a workgroup walks
+// several tiles, whose items hide the exchanges, and the halo arithmetic counts.
+// ms, 16 x 16 against 24 x 24: 12 volumes (470 tiles of 16 x 16) 2.67 / 2.84, 15
+// volumes and 5 images (450) 2.65 / 2.45, 24 volumes (832) 3.84 / 3.26, 48
+// volumes and 16 images 21.5 / 14.0.
+int untuned_class(const std::vector<Problem>& prs) {
+  constexpr long long kCUs = 256;
+  auto demand = [&](int TP, int TQ, bool images) {
+    long long sum = 0;
+    for (const Problem& pr : prs) {
+      long long most = 0;
+      for (int a = 0; a < pr.ndim; ++a) {
+        PassDesc d;
+        pass_geometry(pr, a, &d);
+        const long long row = (d.Nq + kRowTQ - 1) / kRowTQ;
+        const long long t = pr.ndim == 3 ? (long long)((d.Np + TP - 1) / TP) * ((d.Nq + TQ - 1) / TQ)
+                                         : (row + kBatchTeamsPerWg - 1) / kBatchTeamsPerWg;
+        most = t > most ? t : most;
+      }
+      if (images == (pr.ndim == 2)) sum += most;
+    }
+    return sum;
+  };
+  const long long free = kCUs - demand(16, 16, true);
+  for (int k : {4, 3})
+    if (demand(kBatchTP3[k], kBatchTQ3[k], false) <= free) return k;
+  return 4 * demand(kBatchTP3[0], kBatchTQ3[0], false) > 7 * (free > 0 ? free : 0) ? 2 : 0;
 }
 
 int validate_instance(const ggdt_instance& in, Problem* pr) {
@@ -135,9 +177,9 @@ int ggdt_batched_plan(const ggdt_instance* instances, int n, const ggdt_tuning* 
     any_cls = true;  // the classification decides every instance's edge-cost mode
   }
   int kclass = maxC <= kBatchMaxC[0] ? 0 : 1;
-  const bool wide = tuning && (tuning->tile_p == kBatchTile3[2] || tuning->tile_q == kBatchTile3[2]);
+  const bool wide = tuning && (tuning->tile_p == kBatchTP3[2] || tuning->tile_q == kBatchTQ3[2]);
   if (tuning && (tuning->tile_p > 0 || tuning->tile_q > 0) && !wide &&
-      !(tuning->tile_p == kBatchTile3[0] || tuning->tile_q == kBatchTile3[0]))
+      !(tuning->tile_p == kBatchTP3[0] || tuning->tile_q == kBatchTQ3[0]))
     return GGDT_ERR_BAD_PARAM;
   if (wide) {
     // 24 x 24 volume tiles with K = 4: single-channel batches only
@@ -145,8 +187,10 @@ int ggdt_batched_plan(const ggdt_instance* instances, int n, const ggdt_tuning* 
     kclass = 2;
   } else if (tuning && tuning->chunk > 0) {
     if (tuning->chunk == kBatchK3[1] || tuning->chunk == kBatchK2[1]) kclass = 1;
-    else if (tuning->chunk != kBatchK3[0] && tuning->chunk != kBatchK2[0]) return GGDT_ERR_BAD_PARAM;
+    else if (tuning->chunk != kBatchK3[0] && tuning->chunk != kBatchTuneK2) return GGDT_ERR_BAD_PARAM;
   }
+  if (kclass == 0 && !(tuning && (tuning->chunk > 0 || tuning->tile_p > 0 || tuning->tile_q > 0)))
+    kclass = untuned_class(prs);
   if (maxC > kBatchMaxC[kclass]) return kclass == 0 ? GGDT_ERR_BAD_PARAM : GGDT_ERR_UNSUPPORTED;
   int rc = check_device();
   if (rc) return rc;
@@ -204,10 +248,13 @@ int ggdt_batched_plan(const ggdt_instance* instances, int n, const ggdt_tuning* 
       if (rc) return rc;
       d.K = in.ndim == 3 ? kBatchK3[kclass] : kBatchK2[kclass];
       if (in.ndim == 3) {
-        d.TP = d.TQ = kBatchTile3[kclass];
-        d.ntp = (d.Np + d.TP - 1) / d.TP;
-        d.ntq = (d.Nq + d.TQ - 1) / d.TQ;
+        d.TP = kBatchTP3[kclass];
+        d.TQ = kBatchTQ3[kclass];
+      } else if (kclass != 1) {  // teams
+        d.TQ = kRowLanes - 2 * d.K;
       }
+      d.ntp = (d.Np + d.TP - 1) / d.TP;
+      d.ntq = (d.Nq + d.TQ - 1) / d.TQ;
       d.nchunk = (d.Na - 1 + d.K - 1) / d.K;
       base += (unsigned)d.nchunk + 1u;
       const int k = p % 6;

@@ -33,7 +33,7 @@ __global__ __launch_bounds__(kRowLanes) void pass_row_kernel(PassDesc g, unsigne
 template <int RMODE, int NCH, bool REC, int FMT = kImgF32>
 __global__ __launch_bounds__(kTeamThreads) void pass_team_kernel(PassDesc g, unsigned* words,
                                                                  unsigned long long limit) {
-  __shared__ float costs[2 * kTeamChunk];
+  __shared__ float costs[2 * team_chunk(kRowK)];
   __shared__ int fail;
   if (ld_relaxed(words + kWordAbort) != 0u) return;
   if (g.converge && ld_relaxed(words + kWordDone) != 0u) return;  // an earlier iteration changed nothing

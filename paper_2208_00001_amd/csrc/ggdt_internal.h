@@ -173,15 +173,20 @@ constexpr int kRowLanes = 64, kRowK = 16, kRowTQ = kRowLanes - 2 * kRowK, kRowMa
 // channels they take.
 constexpr int kCellTP = 16, kCellTQ = 16, kCellK = 8, kCellMaxC = 3;
 
-// Batched kernel classes: 0 for single-channel batches (3D: thread-per-cell
-// pass on 16 x 16 tiles, K = 8); 1 for up to 4 channels (tile passes, K = 4 /
-// 16); 2 single-channel, chosen by tuning (3D: thread-per-cell pass on 24 x 24
-// tiles, K = 4, less halo arithmetic for twice the exchanges).  Chunk lengths
-// (3D / 2D), 3D tile side, channel limit:
-constexpr int kBatchK3[3] = {8, 4, 4};
-constexpr int kBatchK2[3] = {32, 16, 32};
-constexpr int kBatchTile3[3] = {16, 16, 24};
-constexpr int kBatchMaxC[3] = {1, 4, 1};
+// Batched kernel classes.  Single-channel batches run thread-per-cell passes on
+// volumes (their tile per class) and teams (pass_team.h) on images: 0 and 2 may
+// also be asked for by a tuning; 3 and 4 have smaller tiles, for batches whose
+// tiles then still have a CU each; 2 has less halo arithmetic for twice the
+// exchanges, for batches with several tiles per CU.  Class 1, the tile passes
+// for up to 4 channels.  Chunk lengths (3D / 2D), 3D tile, channel limit:
+constexpr int kBatchClasses = 5;
+constexpr int kBatchK3[kBatchClasses] = {8, 4, 4, 8, 8};
+constexpr int kBatchK2[kBatchClasses] = {kRowK, 16, kRowK, kRowK, kRowK};
+constexpr int kBatchTP3[kBatchClasses] = {16, 16, 24, 8, 8};
+constexpr int kBatchTQ3[kBatchClasses] = {16, 16, 24, 16, 8};
+constexpr int kBatchMaxC[kBatchClasses] = {1, 4, 1, 1, 1};
+constexpr int kBatchTeamsPerWg = 4;  // tiles of an image that a workgroup's teams walk at once
+constexpr int kBatchTuneK2 = 32;     // 2D chunk length by which a tuning may also name class 0
 
 size_t batched_lds_bytes(int kclass, int C, bool has2d, bool has3d);
 int batched_capacity(int kclass, bool rec, size_t lds);

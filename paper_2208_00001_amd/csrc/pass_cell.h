@@ -54,12 +54,12 @@ using CellGeomSmall = CellGeom<8, 8, kCellK>;   // 24 x 24 box, 9 waves
 // launches may choose it): 1.27 computed cells per voxel update instead of
 // 2.15, for twice the exchanges.
 using CellGeomWide = CellGeom<24, 24, 4>;
-constexpr int kCellWideTP = CellGeomWide::TP, kCellWideK = CellGeomWide::K;
-// largest staged array and result buffer over the geometries
-constexpr int kCellStageMax = kCellStage > CellGeomWide::STAGE ? kCellStage : CellGeomWide::STAGE;
-constexpr int kCellResMax = kCellTP * kCellTQ * kCellSCR > CellGeomWide::RES ? kCellTP * kCellTQ * kCellSCR
-                                                                                : CellGeomWide::RES;
-
+// A geometry in a workgroup of kCellThreads threads, whatever its box needs
+// (batched launches): the threads past the box only meet the barriers.
+template <class Geo>
+struct CellGeomPadded : Geo {
+  static constexpr int NT = kCellThreads;
+};
 // Edge cost through offset j from the channels of x (ix) and of its parent (iy).
 template <int MODE, int NCH>
 __device__ __forceinline__ float cell_edge(const PassDesc& g, int j, const float* ix, const float* iy) {
@@ -103,22 +103,12 @@ struct CellLds {
   int* fail;     // one word: item number + 1 of a bounded wait that gave up
 };
 
-// Bytes of one dynamic LDS area holding every array of CellLds, for either
-// geometry.
-constexpr size_t kCellLdsBytes = sizeof(float2) * 2 * kCellThreads +
-                                 sizeof(float) * ((size_t)2 * kCellStageMax + (size_t)kCellResMax) + sizeof(int);
-
-// CellLds carved from one dynamic LDS area of kCellLdsBytes (launches that
-// share the area with other paths).
+// Bytes of one dynamic LDS area for the strided passes, and CellLds carved from
+// it (launches that share the area with other paths).
+constexpr size_t kCellLdsBytes = sizeof(float2) * 2 * kCellThreads + sizeof(int);
 __device__ __forceinline__ CellLds carve_cell_lds(float* lds) {
-  CellLds l;
-  l.pair = reinterpret_cast<float2*>(lds);
-  l.chan = nullptr;
-  l.stD = lds + 4 * kCellThreads;
-  l.stI = l.stD + kCellStageMax;
-  l.res = l.stI + kCellStageMax;
-  l.fail = reinterpret_cast<int*>(l.res + kCellResMax);
-  return l;
+  return CellLds{reinterpret_cast<float2*>(lds), nullptr, nullptr, nullptr, nullptr,
+                 reinterpret_cast<int*>(lds + 4 * kCellThreads)};
 }
 
 template <bool SCANC, int MODE, bool REC, class Geo = CellGeomBase, int FMT = kImgF32, int NCH = 1>
@@ -549,18 +539,13 @@ __device__ __forceinline__ bool run_pass_cell_mode(const PassDesc* gp, unsigned 
   return run_pass_cell<SCANC, kModeGeneral, REC, Geo, FMT, NCH>(gp, xbuf, words, limit, lds, wg, G);
 }
 
-// Layout and requested mode chosen at run time (batched launches).
+// Requested mode chosen at run time, strided layout (batched launches: the passes
+// along a contiguous axis run on scan-major copies; the few in-place ones, where
+// the last axis has one element, give the same values lane by lane).
 template <bool REC, class Geo = CellGeomBase>
 __device__ __forceinline__ bool run_pass_cell_rt(const PassDesc* gp, unsigned long long* xbuf, unsigned* words,
                                                  const unsigned* cls_word, int mode, unsigned long long limit,
                                                  const CellLds& lds, int wg, int G) {
-  if (gp->sa == 1) {
-    if (mode == kModeLam0)
-      return run_pass_cell_mode<true, kModeLam0, REC, Geo>(gp, xbuf, words, cls_word, limit, lds, wg, G);
-    if (mode == kModeLam1C1)
-      return run_pass_cell_mode<true, kModeLam1C1, REC, Geo>(gp, xbuf, words, cls_word, limit, lds, wg, G);
-    return run_pass_cell_mode<true, kModeGeneral, REC, Geo>(gp, xbuf, words, cls_word, limit, lds, wg, G);
-  }
   if (mode == kModeLam0)
     return run_pass_cell_mode<false, kModeLam0, REC, Geo>(gp, xbuf, words, cls_word, limit, lds, wg, G);
   if (mode == kModeLam1C1)

@@ -17,34 +17,40 @@ namespace ggdt {
 namespace dev {
 
 constexpr int kTeamThreads = 4 * kRowLanes;
-// costs of one chunk: [row][offset][lane]
-constexpr int kTeamChunk = kRowK * 3 * kRowLanes;
+// costs of one chunk of K rows: [row][offset][lane]
+constexpr int team_chunk(int K) { return K * 3 * kRowLanes; }
 
-// One 2D pass by workgroup `wg` of G (kTeamThreads threads).  `costs`: two
-// chunks in LDS; `failw`: one LDS word.  False if a bounded wait gave up.
-template <int MODE, int NCH, bool REC, int FMT>
+// One 2D pass by workgroup `wg` of G, each of NTEAM teams (kTeamThreads threads
+// a team).  `costs`: two chunks per team in LDS; `failw`: one LDS word.  False
+// if a bounded wait gave up.
+template <int MODE, int NCH, bool REC, int FMT, int K = kRowK, int NTEAM = 1>
 __device__ __forceinline__ bool run_pass_team(const PassDesc* gp, unsigned long long* xbuf, unsigned* words,
                                               unsigned long long limit, float* costs, int* failw, int wg, int G) {
-  static_assert(MODE != kModeLam0, "lambda 0 has no costs to produce");
-  constexpr int K = kRowK, TQ = kRowTQ;
+  constexpr int TQ = kRowLanes - 2 * K;
+  constexpr bool USE_I = MODE != kModeLam0;  // lambda 0: constant costs, the producers only meet the barriers
   const PassDesc g = *gp;
   const auto gImage = image_of<FMT>(g.image);
   const gmem<const float> gMask = to_gmem(g.mask);
   const gmem<float> gD = to_gmem(g.D);
   const gmem<uint8_t> gRec = to_gmem(g.rec);
   const int lane = threadIdx.x & (kRowLanes - 1);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kRowLanes);
+  const int wave_id = __builtin_amdgcn_readfirstlane(threadIdx.x / kRowLanes);
+  // 0: the team's chain wave, else a producer.  A workgroup's waves go to the four
+  // SIMDs in turn: the rotation gives every team's chain wave another SIMD.
+  const int wave = (wave_id + (wave_id >> 2)) & 3;
+  const int team = wg * NTEAM + (wave_id >> 2), nteam = G * NTEAM;
+  costs += (wave_id >> 2) * 2 * team_chunk(K);
   const int e = max(max(K - lane, lane - (K + TQ - 1)), 0);
   const int own = lane - K;
   const int ntiles = g.ntq;
-  if (wg >= ntiles) return true;
+  if (wg * NTEAM >= ntiles) return true;
   const int Na = g.Na, Nq = g.Nq;
   const long long cstride = g.N;
   if (threadIdx.x == 0) *failw = 0;  // read only after a barrier
 
   if (wave == 0 && (g.init || REC)) {  // first row in scan order
     const int kf = g.sign > 0 ? 0 : Na - 1;
-    for (int tile = wg; tile < ntiles; tile += G) {
+    for (int tile = team; tile < ntiles; tile += nteam) {
       const int q = tile * TQ + own;
       if (e == 0 && q < Nq) {
         const int x = kf * g.sa + q * g.sq;
@@ -56,7 +62,9 @@ __device__ __forceinline__ bool run_pass_team(const PassDesc* gp, unsigned long 
 
   const gmem<const float> dsrc0 = g.init ? gMask : (gmem<const float>)gD;
   const float vscale = g.init ? g.v : 1.0f;
-  const int nmine = (ntiles - wg + G - 1) / G;
+  // rounds of one tile per team; a team without a tile in the last round only
+  // meets the barriers
+  const int nmine = (ntiles - wg * NTEAM + nteam - 1) / nteam;
   const int nitems = g.nchunk * nmine;
   struct Item {
     int c, tile, t0, kk, q, xq;
@@ -65,11 +73,11 @@ __device__ __forceinline__ bool run_pass_team(const PassDesc* gp, unsigned long 
   auto item_of = [&](int n) {
     Item it;
     it.c = n / nmine;
-    it.tile = wg + (n - it.c * nmine) * G;
+    it.tile = team + (n - it.c * nmine) * nteam;
     it.t0 = 1 + it.c * K;
     it.kk = min(K, Na - it.t0);
     it.q = it.tile * TQ - K + lane;
-    it.in = it.q >= 0 && it.q < Nq;
+    it.in = it.q >= 0 && it.q < Nq && it.tile < ntiles;
     it.xq = it.in ? it.q * g.sq : 0;
     return it;
   };
@@ -98,16 +106,16 @@ __device__ __forceinline__ bool run_pass_team(const PassDesc* gp, unsigned long 
         for (int c = 0; c < NCH; ++c) nx[j][c] = gImage[c * cstride + x];
       }
     };
-    if (nitems > 0) fetch(item_of(0));
+    if (USE_I && nitems > 0) fetch(item_of(0));
     for (int n = 0; n <= nitems; ++n) {
-      if (n < nitems) {
+      if (USE_I && n < nitems) {
         float ix[NR + 1][NCH];
 #pragma unroll
         for (int j = 0; j <= NR; ++j)
 #pragma unroll
           for (int c = 0; c < NCH; ++c) ix[j][c] = widen<FMT>(nx[j][c]);
         if (n + 1 < nitems) fetch(item_of(n + 1));
-        float* out = costs + (n & 1) * kTeamChunk + r0 * 3 * kRowLanes + lane;
+        float* out = costs + (n & 1) * team_chunk(K) + r0 * 3 * kRowLanes + lane;
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
           float iy[3][NCH];
@@ -130,7 +138,9 @@ __device__ __forceinline__ bool run_pass_team(const PassDesc* gp, unsigned long 
     return true;
   }
 
-  // Chain wave: item n - 1 in phase n.
+  // Chain wave: item n - 1 in phase n.  Where teams share the SIMDs (NTEAM > 1)
+  // it issues before the producers, which have a whole phase.
+  if (NTEAM > 1) __builtin_amdgcn_s_setprio(3);
   float nd[K + 1];
   auto fetch = [&](const Item& it) {
     const int x0 = xof(it, 0);
@@ -164,7 +174,7 @@ __device__ __forceinline__ bool run_pass_team(const PassDesc* gp, unsigned long 
     }
     if (__any(fail)) *failw = 1;
     if (has_next) fetch(nxt);
-    const float* wc = costs + (n & 1) * kTeamChunk + lane;
+    const float* wc = costs + (n & 1) * team_chunk(K) + lane;
     float res[K];
     int rch[K];
     auto step = [&](int i) {
@@ -173,7 +183,7 @@ __device__ __forceinline__ bool run_pass_team(const PassDesc* gp, unsigned long 
       int choice = 0;
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
-        const float cand = dy[j] + wc[(i * 3 + j) * kRowLanes];
+        const float cand = dy[j] + (USE_I ? wc[(i * 3 + j) * kRowLanes] : g.W0[j]);
         if (REC) {
           choice = cand < best ? 1 + j : choice;
           best = cand < best ? cand : best;
@@ -209,9 +219,10 @@ __device__ __forceinline__ bool run_pass_team(const PassDesc* gp, unsigned long 
       }
     }
     step_barrier();
-    if (*failw) return false;
+    if (*failw) return false;  // (the launch ends: every wave of it returns)
     cur = nxt;
   }
+  if (NTEAM > 1) __builtin_amdgcn_s_setprio(0);
   if (g.converge && __any(chg) && lane == 0)
     __hip_atomic_store(words + kWordChanged, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return true;
@@ -219,18 +230,18 @@ __device__ __forceinline__ bool run_pass_team(const PassDesc* gp, unsigned long 
 
 // Requested mode RMODE falls back to the general formula when the image
 // classification word rules the fast edge cost out.
-template <int RMODE, int NCH, bool REC, int FMT>
+template <int RMODE, int NCH, bool REC, int FMT, int K = kRowK, int NTEAM = 1>
 __device__ __forceinline__ bool run_pass_team_mode(const PassDesc* gp, unsigned long long* xbuf, unsigned* words,
                                                    const unsigned* cls_word, unsigned long long limit, float* costs,
                                                    int* failw, int wg, int G) {
   if (RMODE == kModeGeneral) {
     if (general_n_ok(gp->sqrt_normal, cls_word))
-      return run_pass_team<kModeGeneralN, NCH, REC, FMT>(gp, xbuf, words, limit, costs, failw, wg, G);
-    return run_pass_team<kModeGeneral, NCH, REC, FMT>(gp, xbuf, words, limit, costs, failw, wg, G);
+      return run_pass_team<kModeGeneralN, NCH, REC, FMT, K, NTEAM>(gp, xbuf, words, limit, costs, failw, wg, G);
+    return run_pass_team<kModeGeneral, NCH, REC, FMT, K, NTEAM>(gp, xbuf, words, limit, costs, failw, wg, G);
   }
   if (fast_mode_ok(RMODE, ld_relaxed(cls_word)))
-    return run_pass_team<RMODE, NCH, REC, FMT>(gp, xbuf, words, limit, costs, failw, wg, G);
-  return run_pass_team<kModeGeneral, NCH, REC, FMT>(gp, xbuf, words, limit, costs, failw, wg, G);
+    return run_pass_team<RMODE, NCH, REC, FMT, K, NTEAM>(gp, xbuf, words, limit, costs, failw, wg, G);
+  return run_pass_team<kModeGeneral, NCH, REC, FMT, K, NTEAM>(gp, xbuf, words, limit, costs, failw, wg, G);
 }
 
 }  // namespace dev

@@ -15,6 +15,7 @@ from typing import Optional, Sequence
 import torch
 
 CANDIDATES = (
+    {"wg_per_cu": 0},  # the plan's own choice
     {"chunk": 8, "wg_per_cu": 1},
     {"chunk": 8, "wg_per_cu": 0},
     {"chunk": 4, "wg_per_cu": 1},

@@ -87,3 +87,29 @@ def test_image_backward(shape, C, lam):
     gi, gm = B.ggdt_backward(to_dev(c["image"]), to_dev(rrec), to_dev(W), *args, check=True)
     same(to_host(gm), rgm, "dL/dM")
     same(to_host(gi), rgi, "dL/dI")
+
+
+# volumes whose tiles make the plan take each of its tile sizes (8 x 8, 8 x 16,
+# 16 x 16, 24 x 24), with images of one and of several groups of four tiles, and
+# a volume whose last axis has one element
+BATCHES = [[(9, 100, 100), (33, 70), (9, 30, 1)], [(9, 130, 200), (18, 129)], [(9, 160, 200), (10, 159, 190), (200, 17)],
+           [(9, 160, 200), (9, 150, 210), (10, 159, 200), (9, 170, 200), (60, 300), (9, 1, 20)]]
+
+
+@pytest.mark.parametrize("records", [False, True])
+@pytest.mark.parametrize("batch", range(len(BATCHES)))
+@pytest.mark.parametrize("lam", [0.0, 0.5, 1.0])
+def test_batched_tile_sizes(batch, lam, records):
+    from paper_2208_00001_amd.batched import BatchedPlan
+    cs = [synth.small_case(s, C=1, seed=80 + i, lam=lam, iterations=1) for i, s in enumerate(BATCHES[batch])]
+    inst = [dict(image=to_dev(c["image"]), softmask=to_dev(c["mask"]), spacing=c["spacing"], v=c["v"], lam=c["lam"],
+                 iterations=1, **({"records": True} if records else {})) for c in cs]
+    plan = BatchedPlan(inst)
+    plan.run()
+    plan.check()
+    for c, d in zip(cs, plan.inst):
+        ref, rrec = oracle.ggdt(c["image"], c["mask"], c["spacing"], c["v"], c["lam"], 1, "f32", records=True)
+        same(to_host(d["out"]), ref, c["name"])
+        if records:
+            same(to_host(d["records"]), rrec, c["name"] + " records")
+    plan.close()
