@@ -33,9 +33,10 @@ void prof_after(hipStream_t stream) {
   g_prof_open = false;
 }
 
-hipError_t launch_pass_profiled(const PassDesc& d, int ndim, unsigned* words, hipStream_t stream) {
+hipError_t launch_pass_profiled(const PassDesc& d, int ndim, unsigned* words, hipStream_t stream,
+                                const PassSet* set) {
   prof_before(stream);
-  const hipError_t e = launch_pass(d, ndim, words, g_spin_limit, stream);
+  const hipError_t e = launch_pass(d, ndim, words, g_spin_limit, stream, set);
   prof_after(stream);
   return e;
 }
@@ -275,8 +276,9 @@ static void use_row_geometry(const Problem& pr, PassDesc* d) {
 // 187 x 145 x 93 0.90 / 0.75 / 0.93 at 0.5; at 256^3 1.85 / 0.98 / 0.64 at
 // lambda 1.  (K = 4 loses more in exchanges than it saves in halo cells: 0.62
 // at 128^3, lambda 1, and 0.77 at 256^3.)
-void cell_tile(int Np, int Nq, int* TP, int* TQ) {
-  constexpr int kCUs = 256;
+// `sides`: transforms run side by side.
+void cell_tile(int Np, int Nq, int sides, int* TP, int* TQ) {
+  const int kCUs = 256 / sides;
   const int tp8 = (Np + 7) / 8, tq8 = (Nq + 7) / 8, tq16 = (Nq + 15) / 16;
   *TP = *TQ = 16;
   if ((long long)tp8 * tq8 <= kCUs)
@@ -288,10 +290,10 @@ void cell_tile(int Np, int Nq, int* TP, int* TQ) {
 // The strided passes of volumes of up to kCellMaxC channels run on the
 // thread-per-cell kernel.  (The exchange area of 16 x 16 tiles holds the smaller
 // tiles' too.)
-static void use_cell_geometry(const Problem& pr, PassDesc* d) {
+static void use_cell_geometry(const Problem& pr, PassDesc* d, int sides = 1) {
   if (pr.ndim != 3 || pr.C > kCellMaxC || d->sa == 1) return;
   d->K = kCellK;
-  cell_tile(d->Np, d->Nq, &d->TP, &d->TQ);
+  cell_tile(d->Np, d->Nq, sides, &d->TP, &d->TQ);
   d->ntp = (d->Np + d->TP - 1) / d->TP;
   d->ntq = (d->Nq + d->TQ - 1) / d->TQ;
   d->nchunk = (d->Na - 1 + d->K - 1) / d->K;
@@ -343,6 +345,93 @@ int enqueue_forward(const Problem& pr, const float* image, const float* mask, co
       return GGDT_ERR_HIP;
   }
   (void)tu;
+  return GGDT_OK;
+}
+
+// How many of n transforms of one image run side by side: a power of two.  Of an
+// image, all: its passes take at most 64 waves of the chip's 1024 SIMDs.  Of a
+// volume, as many as shorten the whole by the time of a plane step on the tile
+// that cell_tile gives them (0.73, 0.75 and 0.93 us on 8 x 8, 8 x 16 and 16 x 16
+// tiles at lambda in (0, 1)), times the tiles a CU then has.
+int sides_for(const Problem& pr, int n) {
+  if (pr.ndim == 2) return pr.C <= kRowMaxC ? n : 1;
+  if (pr.C > kCellMaxC) return 1;
+  int best = 1;
+  double best_t = 0.0;
+  for (int j = 1; j <= n; j *= 2) {
+    double t = 0.0;
+    for (int a = 0; a < 3; ++a) {
+      PassDesc d;
+      pass_geometry(pr, a, &d);
+      int TP, TQ;
+      cell_tile(d.Np, d.Nq, j, &TP, &TQ);
+      const long long tiles = (long long)((d.Np + TP - 1) / TP) * ((d.Nq + TQ - 1) / TQ) * j;
+      t += d.Na * (TQ == 8 ? 0.73 : (TP == 8 ? 0.75 : 0.93)) * (double)((tiles + 255) / 256) / j;
+    }
+    if (j == 1 || t < 0.95 * best_t) {
+      best = j;
+      best_t = t;
+    }
+  }
+  return best;
+}
+
+// Workspace of `sides` transforms side by side: header, their exchange words,
+// and (scan_major) their scan-major copies of D and the image's.
+static size_t xbuf_bytes(const Problem& pr) { return workspace_for(pr, Tuning{}) - (size_t)kHeaderWords * 4; }
+size_t sides_workspace(const Problem& pr, int sides) { return (size_t)kHeaderWords * 4 + sides * xbuf_bytes(pr); }
+size_t sides_scan_major_bytes(const Problem& pr, int sides) {
+  if (scan_major_bytes(pr) == 0) return 0;
+  return sides * scan_major_vol_bytes(pr) + ((size_t)pr.C * pr.N * 4 + 255) / 256 * 256;
+}
+
+// The whole forward schedules of `n` masks of one image side by side; ws holds
+// sides_workspace(pr, n) bytes, scan_major (where the passes along the last
+// axis run on copies, else null) sides_scan_major_bytes(pr, n).  The image's
+// scan-major copy is made when `first`.
+int enqueue_sides(const Problem& pr, const float* image, int n, const float* const* masks, float* const* outs,
+                  const float* spacing, float v, float lam, int iterations, void* ws, void* scan_major, bool first,
+                  hipStream_t stream) {
+  unsigned* words = (unsigned*)ws;
+  if (launch_reset(words, (long long)(sides_workspace(pr, n) / 4), stream) != hipSuccess) return GGDT_ERR_HIP;
+  if (launch_classify(image, (long long)pr.C * pr.N, words, stream) != hipSuccess) return GGDT_ERR_HIP;
+  const int D0 = pr.dims[0], D1 = pr.dims[1], D2 = pr.dims[2];
+  ScanMajor sm{};
+  sm.on = scan_major != nullptr;
+  float* sm_d[kMaxSide];
+  if (sm.on) {
+    for (int i = 0; i < n; ++i)
+      sm_d[i] = (float*)((unsigned char*)scan_major + i * scan_major_vol_bytes(pr));
+    sm.image = (unsigned char*)scan_major + n * scan_major_vol_bytes(pr);
+    if (first && image_to_scan_major(pr, image, sm, 4, stream) != hipSuccess) return GGDT_ERR_HIP;
+  }
+  PassSet set{};
+  set.n = n;
+  set.xstride = (long long)(xbuf_bytes(pr) / 8);
+  unsigned base = 0;
+  const int npass = iterations * 2 * pr.ndim;
+  for (int p = 0; p < npass; ++p) {
+    PassDesc d;
+    const int rc = build_pass(pr, image, masks[0], spacing, v, lam, outs[0], nullptr, p, base, &d);
+    if (rc) return rc;
+    use_row_geometry(pr, &d);
+    d.xbuf = (unsigned long long*)(words + kHeaderWords);
+    const int k = p % (2 * pr.ndim);
+    const bool on_copy = sm.on && k >= 4;
+    if (on_copy) use_scan_major(pr, sm.image, sm_d[0], &d);
+    use_cell_geometry(pr, &d, n);
+    base += (unsigned)d.nchunk + 1u;
+    for (int i = 0; i < n; ++i) {
+      set.mask[i] = masks[i];
+      set.D[i] = on_copy ? sm_d[i] : outs[i];
+      if (sm.on && k == 4 && launch_to_scan_major(outs[i], sm_d[i], 4, D0, D1, D2, nullptr, stream) != hipSuccess)
+        return GGDT_ERR_HIP;
+    }
+    if (launch_pass_profiled(d, pr.ndim, words, stream, &set) != hipSuccess) return GGDT_ERR_HIP;
+    for (int i = 0; i < n; ++i)
+      if (sm.on && k == 5 && launch_from_scan_major(sm_d[i], outs[i], 4, D0, D1, D2, nullptr, stream) != hipSuccess)
+        return GGDT_ERR_HIP;
+  }
   return GGDT_OK;
 }
 

@@ -118,7 +118,7 @@ int backward_entry(int ndim, const int* dims, int C, const float* image, const u
       d.TP = 1;
       d.TQ = kRowTQ;
     } else {
-      cell_tile(d.Np, d.Nq, &d.TP, &d.TQ);
+      cell_tile(d.Np, d.Nq, 1, &d.TP, &d.TQ);
     }
     d.ntp = (d.Np + d.TP - 1) / d.TP;
     d.ntq = (d.Nq + d.TQ - 1) / d.TQ;

@@ -6,13 +6,14 @@
 
 namespace ggdt {
 
-using PassKernel = void (*)(PassDesc, unsigned*, unsigned long long);
+using PassKernel = void (*)(PassDesc, PassSet, unsigned*, unsigned long long);
 
 namespace dev {
 
 // One thread per box cell.
 template <class Geo, bool SCANC, int RMODE, bool REC, int FMT, int NCH>
-__global__ __launch_bounds__(Geo::NTCAP) void pass_cell_kernel(PassDesc g, unsigned* words, unsigned long long limit) {
+__global__ __launch_bounds__(Geo::NTCAP) void pass_cell_kernel(PassDesc g, PassSet set, unsigned* words,
+                                                               unsigned long long limit) {
   __shared__ float2 pair[2 * Geo::NT];
   __shared__ int fail;
   CellLds lds{pair, nullptr, nullptr, nullptr, nullptr, &fail};
@@ -30,8 +31,9 @@ __global__ __launch_bounds__(Geo::NTCAP) void pass_cell_kernel(PassDesc g, unsig
   }
   if (ld_relaxed(words + kWordAbort) != 0u) return;
   if (g.converge && ld_relaxed(words + kWordDone) != 0u) return;  // an earlier iteration changed nothing
-  run_pass_cell_mode<SCANC, RMODE, REC, Geo, FMT, NCH>(&g, g.xbuf, words, words + kWordClass, limit, lds,
-                                                  xcd_remap(blockIdx.x, gridDim.x), gridDim.x);
+  int G;
+  const int wg = pick_transform(&g, set, &G);
+  run_pass_cell_mode<SCANC, RMODE, REC, Geo, FMT, NCH>(&g, g.xbuf, words, words + kWordClass, limit, lds, wg, G);
 }
 
 template <class Geo, bool SCANC, bool REC, int FMT, int NCH = 1>

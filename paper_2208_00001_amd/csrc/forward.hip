@@ -12,33 +12,38 @@ namespace {
 using namespace dev;
 
 template <int NDIM, int TP, int TQ, int K, bool SCANC, int RMODE, bool REC>
-__global__ __launch_bounds__(kThreads) void pass_kernel(PassDesc g, unsigned* words, unsigned long long limit) {
+__global__ __launch_bounds__(kThreads) void pass_kernel(PassDesc g, PassSet set, unsigned* words,
+                                                    unsigned long long limit) {
   extern __shared__ __align__(16) float lds[];
   if (ld_relaxed(words + kWordAbort) != 0u) return;
   if (g.converge && ld_relaxed(words + kWordDone) != 0u) return;  // an earlier iteration changed nothing
-  run_pass_mode<NDIM, TP, TQ, K, SCANC, RMODE, REC>(&g, g.xbuf, words, words + kWordClass, limit, lds,
-                                                    xcd_remap(blockIdx.x, gridDim.x), gridDim.x);
+  int G;
+  const int wg = pick_transform(&g, set, &G);
+  run_pass_mode<NDIM, TP, TQ, K, SCANC, RMODE, REC>(&g, g.xbuf, words, words + kWordClass, limit, lds, wg, G);
 }
 
 // 2D passes of images with up to kRowMaxC channels: one wave per 32-cell tile.
 template <int RMODE, int NCH, bool REC, int FMT = kImgF32>
-__global__ __launch_bounds__(kRowLanes) void pass_row_kernel(PassDesc g, unsigned* words, unsigned long long limit) {
+__global__ __launch_bounds__(kRowLanes) void pass_row_kernel(PassDesc g, PassSet set, unsigned* words,
+                                                         unsigned long long limit) {
   if (ld_relaxed(words + kWordAbort) != 0u) return;
   if (g.converge && ld_relaxed(words + kWordDone) != 0u) return;  // an earlier iteration changed nothing
-  run_pass_row_mode<RMODE, NCH, REC, FMT>(&g, g.xbuf, words, words + kWordClass, limit,
-                                          xcd_remap(blockIdx.x, gridDim.x), gridDim.x);
+  int G;
+  const int wg = pick_transform(&g, set, &G);
+  run_pass_row_mode<RMODE, NCH, REC, FMT>(&g, g.xbuf, words, words + kWordClass, limit, wg, G);
 }
 
 // The same with producer waves for the edge costs (lambda above 0).
 template <int RMODE, int NCH, bool REC, int FMT = kImgF32>
-__global__ __launch_bounds__(kTeamThreads) void pass_team_kernel(PassDesc g, unsigned* words,
+__global__ __launch_bounds__(kTeamThreads) void pass_team_kernel(PassDesc g, PassSet set, unsigned* words,
                                                                  unsigned long long limit) {
   __shared__ float costs[2 * team_chunk(kRowK)];
   __shared__ int fail;
   if (ld_relaxed(words + kWordAbort) != 0u) return;
   if (g.converge && ld_relaxed(words + kWordDone) != 0u) return;  // an earlier iteration changed nothing
-  run_pass_team_mode<RMODE, NCH, REC, FMT>(&g, g.xbuf, words, words + kWordClass, limit, costs, &fail,
-                                           xcd_remap(blockIdx.x, gridDim.x), gridDim.x);
+  int G;
+  const int wg = pick_transform(&g, set, &G);
+  run_pass_team_mode<RMODE, NCH, REC, FMT>(&g, g.xbuf, words, words + kWordClass, limit, costs, &fail, wg, G);
 }
 
 bool use_row_path(const PassDesc& d, int ndim) {
@@ -214,15 +219,24 @@ int pass_chunk_for(int ndim, int C, bool scan_contiguous) {
 }
 
 hipError_t launch_pass(const PassDesc& d, int ndim, unsigned* words, unsigned long long spin_limit,
-                       hipStream_t stream) {
+                       hipStream_t stream, const PassSet* sides) {
+  PassSet set{};
+  if (sides) {
+    set = *sides;
+  } else {
+    set.n = 1;
+    set.mask[0] = d.mask;
+    set.D[0] = d.D;
+  }
+  // workgroups of each transform: all of them resident together
+  auto grid_of = [&](int tiles, int cap) { return set.n * (tiles * set.n <= cap ? tiles : cap / set.n); };
   if (use_row_path(d, ndim)) {
     PassKernel fn = select_row_kernel(d);
     if (!fn) return hipErrorInvalidConfiguration;
     const int threads = d.mode == kModeLam0 ? kRowLanes : kTeamThreads;
     const int cap = capacity_for(fn, 0, threads);
-    if (cap <= 0) return hipErrorInvalidConfiguration;
-    const int grid = d.ntq < cap ? d.ntq : cap;
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(threads), 0, stream, d, words, spin_limit);
+    if (cap < set.n) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL(fn, dim3(grid_of(d.ntq, cap)), dim3(threads), 0, stream, d, set, words, spin_limit);
     return hipGetLastError();
   }
   if (ndim == 3 && d.K == kCellK && use_cell_path(d)) {
@@ -233,10 +247,9 @@ hipError_t launch_pass(const PassDesc& d, int ndim, unsigned* words, unsigned lo
     constexpr int threads[3] = {CellGeomBase::NT, CellGeomMid::NT, CellGeomSmall::NT};
     constexpr int threads_cap[3] = {CellGeomBase::NTCAP, CellGeomMid::NTCAP, CellGeomSmall::NTCAP};
     const int cap = capacity_for(fn, 0, threads_cap[geo]);
-    if (cap <= 0) return hipErrorInvalidConfiguration;
-    const int ntiles = d.ntp * d.ntq;
-    const int grid = ntiles < cap ? ntiles : cap;
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(threads[geo]), 0, stream, d, words, spin_limit);
+    if (cap < set.n) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL(fn, dim3(grid_of(d.ntp * d.ntq, cap)), dim3(threads[geo]), 0, stream, d, set, words,
+                       spin_limit);
     return hipGetLastError();
   }
   if (d.img_fmt != kImgF32) return hipErrorInvalidConfiguration;  // 16-bit images: cell and row kernels only
@@ -245,10 +258,8 @@ hipError_t launch_pass(const PassDesc& d, int ndim, unsigned* words, unsigned lo
   const size_t lds = lds_bytes_for(ndim, d.K, d.C, d.sa == 1);
   if (lds == 0 || lds > kMaxLdsBytes) return hipErrorInvalidConfiguration;
   const int cap = capacity_for(fn, lds);
-  if (cap <= 0) return hipErrorInvalidConfiguration;
-  const int ntiles = d.ntp * d.ntq;
-  const int grid = ntiles < cap ? ntiles : cap;
-  hipLaunchKernelGGL(fn, dim3(grid), dim3(kThreads), lds, stream, d, words, spin_limit);
+  if (cap < set.n) return hipErrorInvalidConfiguration;
+  hipLaunchKernelGGL(fn, dim3(grid_of(d.ntp * d.ntq, cap)), dim3(kThreads), lds, stream, d, set, words, spin_limit);
   return hipGetLastError();
 }
 

@@ -41,14 +41,15 @@ void prof_after(hipStream_t stream);
 int build_pass(const Problem& pr, const float* image, const float* mask, const float* spacing, float v, float lam,
                float* out, uint8_t* records, int p, unsigned epoch_base, PassDesc* d);
 // Launch a pass kernel, recording profiling events around it when profiling is on.
-hipError_t launch_pass_profiled(const PassDesc& d, int ndim, unsigned* words, hipStream_t stream);
+hipError_t launch_pass_profiled(const PassDesc& d, int ndim, unsigned* words, hipStream_t stream,
+                                const PassSet* set = nullptr);
 int check_device();
 int make_problem(int ndim, const int* dims, int C, Problem* pr);
 int check_params(int ndim, const float* spacing, float v, float lam, int iterations);
 int check_alias(const void* out, size_t nout, const void* const* ins, const size_t* nins, int nin);
 void tile_shape(const Problem& pr, const Tuning& tu, int* TP, int* TQ);
 void pass_geometry(const Problem& pr, int axis, PassDesc* d);
-void cell_tile(int Np, int Nq, int* TP, int* TQ);
+void cell_tile(int Np, int Nq, int sides, int* TP, int* TQ);
 void edge_constants(const Problem& pr, int axis, const float* spacing, float lam, float* A, float* W0);
 int sqrt_normal_for(const float* A, int n, float lam);  // kSqrtNormal* for the constants A_0..A_{n-1}
 int requested_mode(float lam, int C);
@@ -78,5 +79,13 @@ void* scan_major_in(const Problem& pr, const Tuning& tu, void* ws, size_t wsb);
 int enqueue_forward(const Problem& pr, const float* image, const float* mask, const float* spacing, float v,
                     float lam, int iterations, float* out, uint8_t* records, void* ws, const Tuning& tu,
                     hipStream_t stream, int img_fmt = kImgF32, void* scan_major = nullptr);
+
+// Several masks of one image side by side (see api.cpp).
+int sides_for(const Problem& pr, int n);
+size_t sides_workspace(const Problem& pr, int sides);
+size_t sides_scan_major_bytes(const Problem& pr, int sides);
+int enqueue_sides(const Problem& pr, const float* image, int n, const float* const* masks, float* const* outs,
+                  const float* spacing, float v, float lam, int iterations, void* ws, void* scan_major, bool first,
+                  hipStream_t stream);
 
 }  // namespace ggdt

@@ -109,6 +109,16 @@ struct PassDesc {
   long long d_off;
   long long rec_off;
 };
+// Transforms of one image run side by side by a pass launch: instance i has its
+// own mask, distances and exchange words (xstride words after the instance
+// before); everything else is the descriptor's.
+constexpr int kMaxSide = 4;
+struct PassSet {
+  int n;
+  const float* mask[kMaxSide];
+  float* D[kMaxSide];
+  long long xstride;
+};
 enum PassOp : int { kOpPass = 0, kOpToScanMajor = 1, kOpFromScanMajor = 2 };
 
 // Reverse of one forward pass (see backward_device.h).  Geometry fields as in
@@ -226,10 +236,11 @@ constexpr int kBwdBatchKCell = 8;
 // Returns 0 if no instantiation fits (too many channels).
 int pass_chunk_for(int ndim, int C, bool scan_contiguous);
 
-// Launch one directional pass.  `words` is the workspace header.  Returns a
-// hipError_t (hipErrorInvalidConfiguration if no kernel fits).
+// Launch one directional pass, of the transforms in `set` (null: of the one that
+// d describes).  `words` is the workspace header.  Returns a hipError_t
+// (hipErrorInvalidConfiguration if no kernel fits).
 hipError_t launch_pass(const PassDesc& d, int ndim, unsigned* words, unsigned long long spin_limit,
-                       hipStream_t stream);
+                       hipStream_t stream, const PassSet* set = nullptr);
 
 hipError_t launch_reset(unsigned* ws, long long nwords, hipStream_t stream);
 hipError_t launch_classify(const float* image, long long n, unsigned* words, hipStream_t stream,

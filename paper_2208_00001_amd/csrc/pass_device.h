@@ -45,6 +45,18 @@ __device__ __forceinline__ int xcd_remap(int b, int G) {
   return x * base + min(x, extra) + r;
 }
 
+// This workgroup's transform of a launch over `set`: sets the descriptor's arrays
+// and returns the workgroup's number among the transform's *G workgroups.
+__device__ __forceinline__ int pick_transform(PassDesc* g, const PassSet& set, int* G) {
+  const int b = xcd_remap(blockIdx.x, gridDim.x);
+  *G = (int)gridDim.x / set.n;
+  const int i = b / *G;
+  g->mask = set.mask[i];
+  g->D = set.D[i];
+  g->xbuf += i * set.xstride;
+  return b - i * *G;
+}
+
 // A pointer into global memory, typed as such.  Pointers read out of a
 // descriptor table in memory (the batched launches) carry no address space,
 // and accesses through them compile to generic FLAT instructions; those also

@@ -113,3 +113,27 @@ def test_batched_tile_sizes(batch, lam, records):
         if records:
             same(to_host(d["records"]), rrec, c["name"] + " records")
     plan.close()
+
+
+@pytest.mark.parametrize("shape,C", [((70, 65), 2), ((33, 40), 4), ((20, 33, 40), 1), ((9, 130, 200), 1), ((12, 21, 17), 3),
+                                     ((9, 20, 1), 1), ((11, 14, 13), 4)], ids=str)
+@pytest.mark.parametrize("lam", [0.0, 0.6, 1.0])
+def test_signed_and_filter_side_by_side(shape, C, lam):
+    """The composed operations with the workspace asked for, and with the smaller
+    one that holds one transform at a time."""
+    from paper_2208_00001_amd import binding as B
+    import torch
+    c = synth.small_case(shape, C=C, seed=90 + C, lam=lam, iterations=2)
+    m = (c["mask"] > 0).astype(np.float32)
+    m[tuple(slice(0, max(1, s // 3)) for s in shape)] = 0.0
+    img, md, nd = to_dev(c["image"]), to_dev(m), len(shape)
+    td, te = 0.3, 0.2
+    rs = oracle.signed(c["image"], m, c["spacing"], c["v"], c["lam"], 2)
+    rg = oracle.gsf(c["image"], m, td, te, c["spacing"], c["v"], c["lam"], 2)
+    lib = B.load_library()
+    dims = (3 * __import__("ctypes").c_int)(*shape, *([1] * (3 - nd)))
+    buf = -(-int(np.prod(shape)) * 4 // 256) * 256
+    alone = -(-lib.ggdt_workspace_min_bytes(nd, dims, C) // 256) * 256
+    for ws2, ws4 in ((None, None), *(((torch.empty(alone + n * buf, dtype=torch.uint8, device=DEV)) for n in (2, 4)),)):
+        same(to_host(B.ggdt_signed(img, md, c["spacing"], c["v"], c["lam"], 2, workspace=ws2)), rs, "signed")
+        same(to_host(B.ggdt_gsf(img, md, td, te, c["spacing"], c["v"], c["lam"], 2, workspace=ws4)), rg, "filter")
