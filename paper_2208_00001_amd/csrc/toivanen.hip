@@ -50,6 +50,9 @@ namespace ggdt {
 namespace {
 using namespace dev;
 
+// Four floats at any float's address.
+typedef float float4_u __attribute__((ext_vector_type(4), aligned(4)));
+
 // Thread 0: wait until the neighbour block `dep` has completed `need` steps
 // (polls its progress word; `known` keeps the last count seen), then acquire.
 // Bounded like every wait; false if it gave up or another wait did.
@@ -234,14 +237,15 @@ __device__ __forceinline__ bool ring_sweep(const ToivDesc& d, const RingBlock& k
   constexpr int R1 = R + 1;
   const int G = d.ng, G1 = G + 1;
   const float inf = __builtin_inff();
-  float* rD = lds;               // [S][R1]    D of the block's rows
-  float* rI = rD + S * R1;       // [C][S][R1] their image values
-  float* gD = rI + C * S * R1;   // [S][G1]    D of the ghost rows
-  float* gI = gD + S * G1;       // [C][S][G1]
-  const int gbase = (1 + C) * S * R1;  // gD's offset in the LDS
+  // D and the first channel lie side by side, so that a candidate is one 8-byte
+  // LDS read; the further channels follow.
+  float2* rP = reinterpret_cast<float2*>(lds);           // [S][R1]        (D, I) of the block's rows
+  float* rI = lds + 2 * S * R1;                          // [C - 1][S][R1] their further channels
+  const int gbase = (1 + C) * S * R1;                    // the ghost rows' offset in the LDS (even)
+  float2* gP = reinterpret_cast<float2*>(lds + gbase);   // [S][G1]        (D, I) of the ghost rows
+  float* gI = lds + gbase + 2 * S * G1;                  // [C - 1][S][G1]
   const gmem<const float> I = to_gmem(d.image);
   const gmem<float> D = to_gmem(d.D);
-  const gmem<float> sink = to_gmem(reinterpret_cast<float*>(words + kWordSink));
   unsigned long long* prog = reinterpret_cast<unsigned long long*>(words + kHeaderWords);
   const int Z = d.dims[0], H = d.dims[1], W = d.dims[2], T = d.T;
   const long long N = d.N;
@@ -266,6 +270,8 @@ __device__ __forceinline__ bool ring_sweep(const ToivDesc& d, const RingBlock& k
   // candidate's column (ring offset at slot 0) and ring stride
   const bool edge = image ? (y == (DIR > 0 ? k0.y0 : k0.y1 - 1)) : (z == (DIR > 0 ? k0.z0 : k0.z1 - 1));
   const int estride = edge ? G1 : R1;  // stride of the offsets 0..KG-1
+  // further channels: from a pair's offset o (in floats) at o / 2 + xadj
+  const int xadj_r = 2 * S * R1, xadj_e = edge ? gbase + 2 * S * G1 - gbase / 2 : xadj_r;
   int col[NOFF];
 #pragma unroll
   for (int k = 0; k < NOFF; ++k) {
@@ -273,9 +279,9 @@ __device__ __forceinline__ bool ring_sweep(const ToivDesc& d, const RingBlock& k
     const int zz = z + dz, yy = y + dy;
     const bool there = has_row && zz >= 0 && zz < Z && yy >= 0 && yy < H;
     if (k < KG && edge)
-      col[k] = gbase + (there ? (image ? 0 : yy) : G);
+      col[k] = gbase + 2 * (there ? (image ? 0 : yy) : G);
     else
-      col[k] = there ? r + dz * k0.nry + dy : R;
+      col[k] = 2 * (there ? r + dz * k0.nry + dy : R);
   }
   unsigned long long known = 0;
   // the neighbour's steps up to u_lo + 1: the ghosts of the first step and the first ghost load
@@ -284,8 +290,8 @@ __device__ __forceinline__ bool ring_sweep(const ToivDesc& d, const RingBlock& k
     s_ok[0] = !has_dep || wait_progress(prog, dep, need < end ? need : end, known, words, limit);
   }
   // the rings' D at +inf (the last columns stay so)
-  for (int i = r; i < S * R1; i += NT) rD[i] = inf;
-  for (int i = r; i < S * G1; i += NT) gD[i] = inf;
+  for (int i = r; i < S * R1; i += NT) rP[i] = make_float2(inf, 0.0f);
+  for (int i = r; i < S * G1; i += NT) gP[i] = make_float2(inf, 0.0f);
   __syncthreads();
   if (!s_ok[0]) return false;
   float pD = 0.0f, pI[C];  // the loader's ghost voxel of the current step
@@ -309,109 +315,172 @@ __device__ __forceinline__ bool ring_sweep(const ToivDesc& d, const RingBlock& k
         px = xg;
       } else {
         const int slot = ug & (S - 1);
-        gD[slot * G1 + gcol] = vD;
+        gP[slot * G1 + gcol] = make_float2(vD, vI[0]);
 #pragma unroll
-        for (int c = 0; c < C; ++c) gI[(c * S + slot) * G1 + gcol] = vI[c];
+        for (int c = 1; c < C; ++c) gI[((c - 1) * S + slot) * G1 + gcol] = vI[c];
       }
     }
   }
-  float cD = 0.0f, cI[C];  // the row's own D (previous sweep) and image at the current step
+  // The row's own D (previous sweep) and image, four steps at a time: one
+  // 16-byte load per array and four steps, issued four steps ahead, and one
+  // 16-byte store of the results.  Every lane is on another row, so a 4-byte
+  // access per step would cost a cache-line request per lane, array and step:
+  // 2560 requests a step for 512 rows, which bounded the step.
+  // Group of step u: elements lo(u) .. lo(u) + 3 of the row, in scan order
+  // from the low end (forward) or the high end.
+  auto group_lo = [&](int u) {
+    const int x = (DIR > 0 ? u : T - 1 - u) - t0;
+    return DIR > 0 ? x : x - 3;
+  };
+  // Elements o .. o + 3 of an N-value array, in scan order.  At the array's ends
+  // the load is moved inside and its elements back in place (those outside the
+  // array are not used).
+  auto load4 = [&](const gmem<const float> a, long long o, float* out) {
+    const long long oc = o < 0 ? 0 : (o > N - 4 ? N - 4 : o);
+    const int sh = (int)(o - oc);  // element j lies at oc + sh + j
+    const float4_u v = *(gmem<const float4_u>)(a + oc);
+    const float e[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-  for (int c = 0; c < C; ++c) cI[c] = 0.0f;
-  {
-    const int x = (DIR > 0 ? u_lo : T - 1 - u_lo) - t0;
-    if (has_row && x >= 0 && x < W) {
-      cD = D[row0 + x];
+    for (int j = 0; j < 4; ++j) {
+      float q = e[j];
 #pragma unroll
-      for (int c = 0; c < C; ++c) cI[c] = I[c * N + row0 + x];
+      for (int m = 0; m < 4; ++m) q = sh != 0 && sh + j == m ? e[m] : q;
+      out[DIR > 0 ? j : 3 - j] = q;
     }
-  }
+  };
+  float nD[4], nI[C][4];  // the next group
+  auto fetch_group = [&](int u) {
+    // idle rows read their clamped neighbourhood: the offset stays near the row
+    const int lo = min(max(group_lo(u), -4), W);
+    load4((gmem<const float>)D, row0 + lo, nD);
+#pragma unroll
+    for (int c = 0; c < C; ++c) load4(I + c * N, row0 + lo, nI[c]);
+  };
+  fetch_group(u_lo);
   // complete the loads above, so that a step's wait for its operands counts
   // only the memory operations of the step before
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
 #pragma unroll 1
-  for (int u = u_lo; u <= u_hi; ++u) {
-    const int t = DIR > 0 ? u : T - 1 - u;
-    const bool more = u < u_hi;
-    // the ghost voxel of this step into its slot (loaded a step ago), +inf
-    // where there is none
-    if (loader) {
-      const int slot = u & (S - 1);
-      gD[slot * G1 + gcol] = px >= 0 ? pD : inf;
+  for (int ug = u_lo; ug <= u_hi; ug += 4) {
+    float oD[4], oI[C][4], res[4];
 #pragma unroll
-      for (int c = 0; c < C; ++c) gI[(c * S + slot) * G1 + gcol] = pI[c];
+    for (int i = 0; i < 4; ++i) {
+      oD[i] = nD[i];
+      res[i] = 0.0f;
+#pragma unroll
+      for (int c = 0; c < C; ++c) oI[c][i] = nI[c][i];
     }
-    // the next step's loads, issued by every thread at a clamped index
-    // (their values unused where the voxel does not exist), so that no wait
-    // before this step's arithmetic has to include them
-    const int xn = t + DIR - t0, xg = t + DIR - tg0;
-    const long long on = row0 + min(max(xn, 0), W - 1);
-    const long long gn = (loader ? grow0 : row0) + min(max(xg, 0), W - 1);
-    const float nD = D[on], qD = D[gn];
-    float nI[C], qI[C];
+    fetch_group(ug + 4);
+    int pending = 0;  // steps of the group not stored yet
 #pragma unroll
-    for (int c = 0; c < C; ++c) {
-      nI[c] = I[c * N + on];
-      qI[c] = I[c * N + gn];
-    }
-    const int x = t - t0;
-    const bool active = has_row && x >= 0 && x < W;
-    float best = cD;
+    for (int i = 0; i < 4; ++i) {
+      const int u = ug + i;
+      if (u > u_hi) break;
+      const int t = DIR > 0 ? u : T - 1 - u;
+      const float cD = oD[i];
+      float cI[C];
 #pragma unroll
-    for (int k = 0; k < NOFF; ++k) {
-      // steps back to the neighbour's hyperplane, and its ring slot (uniform)
-      const int a = -(4 * ring_off<NOFF>(k, 0) + 2 * ring_off<NOFF>(k, 1) + ring_off<NOFF>(k, 2));
-      const int slot = (u - a) & (S - 1);
-      const int stride = k < KG ? estride : R1;
-      const int cs = S * stride;  // from D to the image values, and between channels
-      const int offD = col[k] + slot * stride;
-      const int offI = offD + cs;
-      const float dv = lds[offD];
-      const float d0 = cI[0] - lds[offI];
-      float w;
-      if (MODE == kModeLam1C1) {
-        w = fabsf(d0);  // = sqrtf(fl(d0 * d0)) for the classified image (no tiny or huge values)
-      } else {
-        float g = d0 * d0;
+      for (int c = 0; c < C; ++c) cI[c] = oI[c][i];
+      const bool more = u < u_hi;
+      // the ghost voxel of this step into its slot (loaded a step ago), +inf
+      // where there is none
+      if (loader) {
+        const int slot = u & (S - 1);
+        gP[slot * G1 + gcol] = make_float2(px >= 0 ? pD : inf, pI[0]);
 #pragma unroll
-        for (int c = 1; c < C; ++c) {
-          const float dc = cI[c] - lds[offI + c * cs];
-          g = fmaf(dc, dc, g);
-        }
-        w = general_root<MODE, (C > 1)>(fmaf(d.lam, g, d.A[k]));
+        for (int c = 1; c < C; ++c) gI[((c - 1) * S + slot) * G1 + gcol] = pI[c];
       }
-      const float cand = dv + w;
-      if (cand < best) best = cand;
-    }
-    {
-      const int slot = u & (S - 1);
-      rD[slot * R1 + r] = active ? best : inf;
+      // the next step's ghost voxel, at a clamped index (its values unused where
+      // the voxel does not exist)
+      const int xg = t + DIR - tg0;
+      float qD = 0.0f, qI[C];
 #pragma unroll
-      for (int c = 0; c < C; ++c) rI[(c * S + slot) * R1 + r] = cI[c];
-    }
-    // the result, stored by every thread (idle ones to the sink word)
-    *(active ? &D[row0 + x] : sink) = best;
-    cD = nD;
-    pD = qD;
+      for (int c = 0; c < C; ++c) qI[c] = 0.0f;
+      if (loader) {
+        const long long gn = grow0 + min(max(xg, 0), W - 1);
+        qD = D[gn];
 #pragma unroll
-    for (int c = 0; c < C; ++c) {
-      cI[c] = nI[c];
-      pI[c] = qI[c];
+        for (int c = 0; c < C; ++c) qI[c] = I[c * N + gn];
+      }
+      const int x = t - t0;
+      const bool active = has_row && x >= 0 && x < W;
+      // A row's hyperplanes take W of a sweep's steps: a wave whose rows are all
+      // idle leaves the candidates out (2 y spans twice the rows, so at W = H half
+      // the waves of a plane are idle at any step).
+      float best = cD;
+      if (__builtin_amdgcn_ballot_w64(active) != 0ull) {
+        float low = inf;  // smallest candidate; a NaN one is ignored
+#pragma unroll
+        for (int k = 0; k < NOFF; ++k) {
+          // steps back to the neighbour's hyperplane, and its ring slot (uniform)
+          const int a = -(4 * ring_off<NOFF>(k, 0) + 2 * ring_off<NOFF>(k, 1) + ring_off<NOFF>(k, 2));
+          const int slot = (u - a) & (S - 1);
+          const int stride = k < KG ? estride : R1;
+          const int off = col[k] + 2 * slot * stride;
+          const float2 nb = *reinterpret_cast<const float2*>(lds + off);
+          const float d0 = cI[0] - nb.y;
+          float w;
+          if (MODE == kModeLam1C1) {
+            w = fabsf(d0);  // = sqrtf(fl(d0 * d0)) for the classified image (no tiny or huge values)
+          } else {
+            float g = d0 * d0;
+#pragma unroll
+            for (int c = 1; c < C; ++c) {
+              const float dc = cI[c] - lds[off / 2 + (k < KG ? xadj_e : xadj_r) + (c - 1) * S * stride];
+              g = fmaf(dc, dc, g);
+            }
+            w = general_root<MODE, (C > 1)>(fmaf(d.lam, g, d.A[k]));
+          }
+          low = fminf(low, nb.x + w);
+        }
+        best = low < cD ? low : cD;
+      }
+      {
+        const int slot = u & (S - 1);
+        rP[slot * R1 + r] = make_float2(active ? best : inf, cI[0]);
+#pragma unroll
+        for (int c = 1; c < C; ++c) rI[((c - 1) * S + slot) * R1 + r] = cI[c];
+      }
+      res[i] = best;
+      ++pending;
+      pD = qD;
+#pragma unroll
+      for (int c = 0; c < C; ++c) pI[c] = qI[c];
+      px = loader && more && xg >= 0 && xg < W ? xg : -1;
+      const bool publish = (u + 1 - u_lo) % d.publish == 0 && more;
+      // the results: a whole group inside the row as one store, else one by one
+      if (i == 3 || publish || !more) {
+        const int lo = DIR > 0 ? x - 3 : x;
+        if (i == 3 && pending == 4 && has_row && lo >= 0 && lo + 3 < W) {
+          float4_u v;
+          v.x = DIR > 0 ? res[0] : res[3];
+          v.y = DIR > 0 ? res[1] : res[2];
+          v.z = DIR > 0 ? res[2] : res[1];
+          v.w = DIR > 0 ? res[3] : res[0];
+          *(gmem<float4_u>)(D + row0 + lo) = v;
+        } else if (has_row) {
+#pragma unroll
+          for (int m = 0; m <= i; ++m) {
+            const int xm = x - DIR * (i - m);
+            if (m > i - pending && xm >= 0 && xm < W) D[row0 + xm] = res[m];
+          }
+        }
+        pending = 0;
+      }
+      // the neighbour's progress the next step's ghost load needs
+      if (r == 0) {
+        const unsigned long long need = base + (unsigned long long)(u + 3);
+        s_ok[u & 1] = !(has_dep && more) || wait_progress(prog, dep, need < end ? need : end, known, words, limit);
+      }
+      if (publish) {
+        __syncthreads();
+        if (r == 0) publish_progress(prog, b, base + (unsigned long long)(u + 1));
+      } else {
+        lds_barrier();
+      }
+      if (!s_ok[u & 1]) return false;
     }
-    px = loader && more && xg >= 0 && xg < W ? xg : -1;
-    // the neighbour's progress the next step's ghost load needs
-    if (r == 0) {
-      const unsigned long long need = base + (unsigned long long)(u + 3);
-      s_ok[u & 1] = !(has_dep && more) || wait_progress(prog, dep, need < end ? need : end, known, words, limit);
-    }
-    if ((u + 1 - u_lo) % d.publish == 0 && more) {
-      __syncthreads();
-      if (r == 0) publish_progress(prog, b, base + (unsigned long long)(u + 1));
-    } else {
-      lds_barrier();
-    }
-    if (!s_ok[u & 1]) return false;
   }
   __syncthreads();
   if (r == 0) publish_progress(prog, b, end);
@@ -544,7 +613,8 @@ int toivanen_plan(ToivDesc* d, long long words) {
     d->threads = nt;
     const void* fn = ring_fn(d->noff, d->C, nt, d->mode);
     const size_t lds = ring_lds(*d);
-    if (fn && rows <= 1024 && lds <= 160 * 1024 && nb <= words) {
+    // (the ring form loads four values at a time)
+    if (fn && rows <= 1024 && lds <= 160 * 1024 && nb <= words && d->N >= 4) {
       const int cap = capacity(fn, nt, lds);
       if (cap <= 0) return GGDT_ERR_HIP;
       if (nb <= cap) {

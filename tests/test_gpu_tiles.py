@@ -137,3 +137,16 @@ def test_signed_and_filter_side_by_side(shape, C, lam):
     for ws2, ws4 in ((None, None), *(((torch.empty(alone + n * buf, dtype=torch.uint8, device=DEV)) for n in (2, 4)),)):
         same(to_host(B.ggdt_signed(img, md, c["spacing"], c["v"], c["lam"], 2, workspace=ws2)), rs, "signed")
         same(to_host(B.ggdt_gsf(img, md, td, te, c["spacing"], c["v"], c["lam"], 2, workspace=ws4)), rg, "filter")
+
+
+@pytest.mark.parametrize("shape", [(3, 4, w) for w in (1, 2, 3, 4, 5, 7, 9)] + [(1, 1, 4), (9, 70, 6), (2, 300, 11)] +
+                         [(5, w) for w in (2, 3, 4, 6)] + [(270, 5), (513, 33)], ids=str)
+@pytest.mark.parametrize("C,lam", [(1, 1.0), (2, 0.5)])
+def test_toivanen_row_ends(shape, C, lam):
+    """Rows shorter and longer than the four elements moved at a time, first and
+    last rows of the array, several blocks and sweeps."""
+    from paper_2208_00001_amd import binding as B
+    c = synth.small_case(shape, C=C, seed=95, lam=lam, iterations=2)
+    args = (c["spacing"], c["v"], c["lam"], 2)
+    ref = oracle.toivanen(c["image"], c["mask"], *args, "f32")
+    same(to_host(B.ggdt_toivanen(to_dev(c["image"]), to_dev(c["mask"]), *args, check=True)), ref, c["name"])
