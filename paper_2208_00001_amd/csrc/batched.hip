@@ -70,17 +70,19 @@ __device__ __attribute__((noinline)) bool run_layout_op(const PassDesc* gp, unsi
 // A 2D pass of a single-channel image: the workgroup's 16 waves are four teams.
 constexpr int kBatchTeams = kBatchThreads / kTeamThreads;
 static_assert(kBatchTeams == kBatchTeamsPerWg, "the plan's workgroup split counts a workgroup's teams");
-template <int K, bool REC>
+template <int K, bool REC, bool SCANC>
 __device__ __forceinline__ bool run_pass_teams(const PassDesc* gp, unsigned long long* xbuf, unsigned* words,
                                                const unsigned* cls, int mode, unsigned long long limit, float* lds,
                                                int wg, int G) {
   constexpr int NT = kBatchTeams;
   int* failw = reinterpret_cast<int*>(lds + NT * 2 * team_chunk(K));
   if (mode == kModeLam0)
-    return run_pass_team_mode<kModeLam0, 1, REC, kImgF32, K, NT>(gp, xbuf, words, cls, limit, lds, failw, wg, G);
+    return run_pass_team_mode<kModeLam0, 1, REC, kImgF32, SCANC, K, NT>(gp, xbuf, words, cls, limit, lds, failw, wg, G);
   if (mode == kModeLam1C1)
-    return run_pass_team_mode<kModeLam1C1, 1, REC, kImgF32, K, NT>(gp, xbuf, words, cls, limit, lds, failw, wg, G);
-  return run_pass_team_mode<kModeGeneral, 1, REC, kImgF32, K, NT>(gp, xbuf, words, cls, limit, lds, failw, wg, G);
+    return run_pass_team_mode<kModeLam1C1, 1, REC, kImgF32, SCANC, K, NT>(gp, xbuf, words, cls, limit, lds, failw, wg,
+                                                                          G);
+  return run_pass_team_mode<kModeGeneral, 1, REC, kImgF32, SCANC, K, NT>(gp, xbuf, words, cls, limit, lds, failw, wg,
+                                                                         G);
 }
 
 // Geo: tile geometry of the thread-per-cell pass for 3D instances, whose 2D
@@ -117,7 +119,8 @@ __global__ __launch_bounds__(kBatchThreads) void batched_kernel(const BatchInst*
       else
         ok = run_pass_rt<3, kTP3, kTQ3, K3, REC>(gp, xbuf, words, cls, in.mode, limit, lds, wg, in.nwg);
     } else if constexpr (CELL) {
-      ok = run_pass_teams<K2, REC>(gp, xbuf, words, cls, in.mode, limit, lds, wg, in.nwg);
+      ok = gp->sa == 1 ? run_pass_teams<K2, REC, true>(gp, xbuf, words, cls, in.mode, limit, lds, wg, in.nwg)
+                       : run_pass_teams<K2, REC, false>(gp, xbuf, words, cls, in.mode, limit, lds, wg, in.nwg);
     } else {
       ok = run_pass_rt<2, 1, kTQ2, K2, REC>(gp, xbuf, words, cls, in.mode, limit, lds, wg, in.nwg);
     }

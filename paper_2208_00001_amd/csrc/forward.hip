@@ -22,19 +22,8 @@ __global__ __launch_bounds__(kThreads) void pass_kernel(PassDesc g, PassSet set,
   run_pass_mode<NDIM, TP, TQ, K, SCANC, RMODE, REC>(&g, g.xbuf, words, words + kWordClass, limit, lds, wg, G);
 }
 
-// 2D passes of images with up to kRowMaxC channels: one wave per 32-cell tile.
-template <int RMODE, int NCH, bool REC, int FMT = kImgF32>
-__global__ __launch_bounds__(kRowLanes) void pass_row_kernel(PassDesc g, PassSet set, unsigned* words,
-                                                         unsigned long long limit) {
-  if (ld_relaxed(words + kWordAbort) != 0u) return;
-  if (g.converge && ld_relaxed(words + kWordDone) != 0u) return;  // an earlier iteration changed nothing
-  int G;
-  const int wg = pick_transform(&g, set, &G);
-  run_pass_row_mode<RMODE, NCH, REC, FMT>(&g, g.xbuf, words, words + kWordClass, limit, wg, G);
-}
-
-// The same with producer waves for the edge costs (lambda above 0).
-template <int RMODE, int NCH, bool REC, int FMT = kImgF32>
+// 2D passes of images with up to kRowMaxC channels: a team of waves per 32-cell tile.
+template <int RMODE, int NCH, bool REC, int FMT, bool SCANC>
 __global__ __launch_bounds__(kTeamThreads) void pass_team_kernel(PassDesc g, PassSet set, unsigned* words,
                                                                  unsigned long long limit) {
   __shared__ float costs[2 * team_chunk(kRowK)];
@@ -43,25 +32,30 @@ __global__ __launch_bounds__(kTeamThreads) void pass_team_kernel(PassDesc g, Pas
   if (g.converge && ld_relaxed(words + kWordDone) != 0u) return;  // an earlier iteration changed nothing
   int G;
   const int wg = pick_transform(&g, set, &G);
-  run_pass_team_mode<RMODE, NCH, REC, FMT>(&g, g.xbuf, words, words + kWordClass, limit, costs, &fail, wg, G);
+  run_pass_team_mode<RMODE, NCH, REC, FMT, SCANC>(&g, g.xbuf, words, words + kWordClass, limit, costs, &fail, wg, G);
 }
 
 bool use_row_path(const PassDesc& d, int ndim) {
   return ndim == 2 && d.TP == 1 && d.TQ == kRowTQ && d.K == kRowK && d.C >= 1 && d.C <= kRowMaxC && d.ntp == 1;
 }
 
-template <int NCH, bool REC, int FMT = kImgF32>
-PassKernel select_row_mode(int mode) {
-  if (mode == kModeLam0) return pass_row_kernel<kModeLam0, NCH, REC, FMT>;
-  if (NCH == 1 && mode == kModeLam1C1) return pass_team_kernel<kModeLam1C1, 1, REC, FMT>;
-  return pass_team_kernel<kModeGeneral, NCH, REC, FMT>;
+template <int NCH, bool REC, int FMT, bool SCANC>
+PassKernel select_row_layout(int mode) {
+  if (mode == kModeLam0) return pass_team_kernel<kModeLam0, NCH, REC, FMT, SCANC>;
+  if (NCH == 1 && mode == kModeLam1C1) return pass_team_kernel<kModeLam1C1, 1, REC, FMT, SCANC>;
+  return pass_team_kernel<kModeGeneral, NCH, REC, FMT, SCANC>;
+}
+
+template <int NCH, bool REC, int FMT>
+PassKernel select_row_mode(const PassDesc& d) {
+  return d.sa == 1 ? select_row_layout<NCH, REC, FMT, true>(d.mode) : select_row_layout<NCH, REC, FMT, false>(d.mode);
 }
 
 template <bool REC, int FMT = kImgF32>
 PassKernel select_row_channels(const PassDesc& d) {
-  if (d.C == 1) return select_row_mode<1, REC, FMT>(d.mode);
-  if (d.C == 2) return select_row_mode<2, REC, FMT>(d.mode);
-  return select_row_mode<3, REC, FMT>(d.mode);
+  if (d.C == 1) return select_row_mode<1, REC, FMT>(d);
+  if (d.C == 2) return select_row_mode<2, REC, FMT>(d);
+  return select_row_mode<3, REC, FMT>(d);
 }
 
 // 16-bit images: plain forward passes only (no records).
@@ -233,7 +227,7 @@ hipError_t launch_pass(const PassDesc& d, int ndim, unsigned* words, unsigned lo
   if (use_row_path(d, ndim)) {
     PassKernel fn = select_row_kernel(d);
     if (!fn) return hipErrorInvalidConfiguration;
-    const int threads = d.mode == kModeLam0 ? kRowLanes : kTeamThreads;
+    const int threads = kTeamThreads;
     const int cap = capacity_for(fn, 0, threads);
     if (cap < set.n) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(fn, dim3(grid_of(d.ntq, cap)), dim3(threads), 0, stream, d, set, words, spin_limit);

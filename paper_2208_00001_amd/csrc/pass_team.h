@@ -20,13 +20,21 @@ constexpr int kTeamThreads = 4 * kRowLanes;
 // costs of one chunk of K rows: [row][offset][lane]
 constexpr int team_chunk(int K) { return K * 3 * kRowLanes; }
 
+// Four elements of a row at any element's address (passes along the contiguous
+// axis).
+typedef float float4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned uint4_a1 __attribute__((ext_vector_type(4), aligned(1)));
+
 // One 2D pass by workgroup `wg` of G, each of NTEAM teams (kTeamThreads threads
 // a team).  `costs`: two chunks per team in LDS; `failw`: one LDS word.  False
-// if a bounded wait gave up.
-template <int MODE, int NCH, bool REC, int FMT, int K = kRowK, int NTEAM = 1>
+// if a bounded wait gave up.  SCANC: the scan axis is the contiguous one; every
+// lane is then on another memory row, and a full chunk moves by 16-byte pieces
+// of it instead of one cache-line request per lane and element.
+template <int MODE, int NCH, bool REC, int FMT, bool SCANC, int K = kRowK, int NTEAM = 1>
 __device__ __forceinline__ bool run_pass_team(const PassDesc* gp, unsigned long long* xbuf, unsigned* words,
                                               unsigned long long limit, float* costs, int* failw, int wg, int G) {
   constexpr int TQ = kRowLanes - 2 * K;
+  static_assert(!SCANC || K == 16, "four 16-byte pieces per chunk");
   constexpr bool USE_I = MODE != kModeLam0;  // lambda 0: constant costs, the producers only meet the barriers
   const PassDesc g = *gp;
   const auto gImage = image_of<FMT>(g.image);
@@ -98,6 +106,28 @@ __device__ __forceinline__ bool run_pass_team(const PassDesc* gp, unsigned long 
     // a lane outside the image gives costs that no cell uses.
     auto fetch = [&](const Item& it) {
       const int x0 = xof(it, 0);
+      if constexpr (SCANC && FMT == kImgF32) {
+        if (it.kk == K) {
+          // rows r0 .. r0 + 3, and r0 + 4 .. (the last producer: 13 .. 16)
+          const int r1 = min(r0 + 4, K - 3);
+          const bool up = g.sign > 0;
+#pragma unroll
+          for (int c = 0; c < NCH; ++c) {
+            const gmem<const float> a = gImage + c * cstride;
+            const float4_a4 v = *(gmem<const float4_a4>)(a + (up ? x0 + r0 : x0 - r0 - 3));
+            const float4_a4 w = *(gmem<const float4_a4>)(a + (up ? x0 + r1 : x0 - r1 - 3));
+            nx[0][c] = up ? v.x : v.w;
+            nx[1][c] = up ? v.y : v.z;
+            nx[2][c] = up ? v.z : v.y;
+            nx[3][c] = up ? v.w : v.x;
+            const float w0 = up ? w.x : w.w, w3 = up ? w.w : w.x;
+            nx[4][c] = r1 == r0 + 4 ? w0 : w3;
+            nx[5][c] = up ? w.y : w.z;
+            nx[6][c] = up ? w.z : w.y;
+          }
+          return;
+        }
+      }
 #pragma unroll
       for (int j = 0; j <= NR; ++j) {
         int x = it.in ? x0 + min(r0 + j, it.kk) * rstep : 0;
@@ -144,6 +174,21 @@ __device__ __forceinline__ bool run_pass_team(const PassDesc* gp, unsigned long 
   float nd[K + 1];
   auto fetch = [&](const Item& it) {
     const int x0 = xof(it, 0);
+    if constexpr (SCANC) {
+      if (it.kk == K) {
+        const bool up = g.sign > 0;
+        nd[0] = dsrc0[x0];
+#pragma unroll
+        for (int m = 0; m < K; m += 4) {
+          const float4_a4 v = *(gmem<const float4_a4>)(dsrc0 + (up ? x0 + 1 + m : x0 - 4 - m));
+          nd[m + 1] = up ? v.x : v.w;
+          nd[m + 2] = up ? v.y : v.z;
+          nd[m + 3] = up ? v.z : v.y;
+          nd[m + 4] = up ? v.w : v.x;
+        }
+        return;
+      }
+    }
     const int last = it.in ? it.kk - e : -1;  // the lane needs rows 0 .. last
 #pragma unroll
     for (int j = 0; j <= K; ++j) {
@@ -208,13 +253,45 @@ __device__ __forceinline__ bool run_pass_team(const PassDesc* gp, unsigned long 
     if (cur.in && e == 0 && !fail) {
       unsigned long long* xout = xbuf + (size_t)(c & 1) * ntiles * TQ + (size_t)cur.tile * TQ;
       st64_relaxed(xout + own, ((unsigned long long)(epoch_in + 1u) << 32) | __float_as_uint(dcur));
+      bool done = false;
+      if constexpr (SCANC) {
+        if (kk == K) {
+          const bool up = g.sign > 0;
+          const int x1 = xof(cur, 1), xk = up ? x1 : x1 - (K - 1);  // the chunk's lowest element
 #pragma unroll
-      for (int i = 0; i < K; ++i) {
-        if (i < kk) {
-          const int x = xof(cur, i + 1);
-          chg |= res[i] < dd[i + 1];
-          gD[x] = res[i];
-          if (REC && g.rec) gRec[x] = (uint8_t)rch[i];
+          for (int m = 0; m < K; m += 4) {
+            float4_a4 v;
+            v.x = up ? res[m] : res[K - 1 - m];
+            v.y = up ? res[m + 1] : res[K - 2 - m];
+            v.z = up ? res[m + 2] : res[K - 3 - m];
+            v.w = up ? res[m + 3] : res[K - 4 - m];
+            *(gmem<float4_a4>)(gD + xk + m) = v;
+          }
+#pragma unroll
+          for (int i = 0; i < K; ++i) chg |= res[i] < dd[i + 1];
+          if (REC && g.rec) {
+            unsigned w[4];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+              w[m] = 0u;
+#pragma unroll
+              for (int i = 0; i < 4; ++i)
+                w[m] |= (unsigned)(up ? rch[4 * m + i] : rch[K - 1 - 4 * m - i]) << (8 * i);
+            }
+            *(gmem<uint4_a1>)(gRec + xk) = uint4_a1{w[0], w[1], w[2], w[3]};
+          }
+          done = true;
+        }
+      }
+      if (!done) {
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+          if (i < kk) {
+            const int x = xof(cur, i + 1);
+            chg |= res[i] < dd[i + 1];
+            gD[x] = res[i];
+            if (REC && g.rec) gRec[x] = (uint8_t)rch[i];
+          }
         }
       }
     }
@@ -230,18 +307,18 @@ __device__ __forceinline__ bool run_pass_team(const PassDesc* gp, unsigned long 
 
 // Requested mode RMODE falls back to the general formula when the image
 // classification word rules the fast edge cost out.
-template <int RMODE, int NCH, bool REC, int FMT, int K = kRowK, int NTEAM = 1>
+template <int RMODE, int NCH, bool REC, int FMT, bool SCANC, int K = kRowK, int NTEAM = 1>
 __device__ __forceinline__ bool run_pass_team_mode(const PassDesc* gp, unsigned long long* xbuf, unsigned* words,
                                                    const unsigned* cls_word, unsigned long long limit, float* costs,
                                                    int* failw, int wg, int G) {
   if (RMODE == kModeGeneral) {
     if (general_n_ok(gp->sqrt_normal, cls_word))
-      return run_pass_team<kModeGeneralN, NCH, REC, FMT, K, NTEAM>(gp, xbuf, words, limit, costs, failw, wg, G);
-    return run_pass_team<kModeGeneral, NCH, REC, FMT, K, NTEAM>(gp, xbuf, words, limit, costs, failw, wg, G);
+      return run_pass_team<kModeGeneralN, NCH, REC, FMT, SCANC, K, NTEAM>(gp, xbuf, words, limit, costs, failw, wg, G);
+    return run_pass_team<kModeGeneral, NCH, REC, FMT, SCANC, K, NTEAM>(gp, xbuf, words, limit, costs, failw, wg, G);
   }
   if (fast_mode_ok(RMODE, ld_relaxed(cls_word)))
-    return run_pass_team<RMODE, NCH, REC, FMT, K, NTEAM>(gp, xbuf, words, limit, costs, failw, wg, G);
-  return run_pass_team<kModeGeneral, NCH, REC, FMT, K, NTEAM>(gp, xbuf, words, limit, costs, failw, wg, G);
+    return run_pass_team<RMODE, NCH, REC, FMT, SCANC, K, NTEAM>(gp, xbuf, words, limit, costs, failw, wg, G);
+  return run_pass_team<kModeGeneral, NCH, REC, FMT, SCANC, K, NTEAM>(gp, xbuf, words, limit, costs, failw, wg, G);
 }
 
 }  // namespace dev
