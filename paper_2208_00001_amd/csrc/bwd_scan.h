@@ -20,7 +20,7 @@
 #pragma once
 
 #include "pass_cell.h"
-#include "pass_row.h"
+#include "pass_team.h"
 
 namespace ggdt {
 namespace dev {
@@ -171,7 +171,10 @@ __device__ __forceinline__ bool run_bwd_scan_cell(const BwdDesc& g, unsigned lon
 }
 
 // The scan of a 2D pass, one wave per 32-cell tile (see pass_row.h): the three
-// possible children are the adjacent lanes, moved by whole-wave shifts.
+// possible children are the adjacent lanes, moved by whole-wave shifts.  SCANC:
+// along the contiguous axis, where a full chunk moves by 16-byte pieces of each
+// lane's memory row (as in pass_team.h).
+template <bool SCANC>
 __device__ __forceinline__ bool run_bwd_scan_row(const BwdDesc& g, unsigned long long* xbuf, unsigned* words,
                                                  unsigned long long limit, int wg, int G) {
   constexpr int K = kRowK, TQ = kRowTQ;
@@ -218,12 +221,37 @@ __device__ __forceinline__ bool run_bwd_scan_row(const BwdDesc& g, unsigned long
   // a clamped, in-bounds address and dropped where consumed.
   float nA[K + 1];
   int nR[K + 1];
+  unsigned nRw[4] = {0u, 0u, 0u, 0u};  // records of rows 1 .. K of a full chunk, in memory order
+  bool nfull = false;
   int nlast = -1;  // the last row the lane needs
+  const bool up = g.sign < 0;  // rows ascend in memory (the reverse walks against the scan)
   auto fetch = [&](const Item& it) {
     const int x0 = xof(it, 0);
     const int step = -g.sign * g.sa;
     const int last = it.in ? it.kk - e : -1;
     nlast = last;
+    if constexpr (SCANC) {
+      nfull = it.kk == K;
+      if (nfull) {
+        nA[0] = gAin[x0];
+        nR[0] = gRec[x0];
+        const int xk = up ? x0 + 1 : x0 - K;
+#pragma unroll
+        for (int m = 0; m < K; m += 4) {
+          const float4_a4 v = *(gmem<const float4_a4>)(gAin + (up ? xk + m : xk + K - 4 - m));
+          nA[m + 1] = up ? v.x : v.w;
+          nA[m + 2] = up ? v.y : v.z;
+          nA[m + 3] = up ? v.z : v.y;
+          nA[m + 4] = up ? v.w : v.x;
+        }
+        const uint4_a1 w = *(gmem<const uint4_a1>)(gRec + xk);
+        nRw[0] = w.x;
+        nRw[1] = w.y;
+        nRw[2] = w.z;
+        nRw[3] = w.w;
+        return;
+      }
+    }
 #pragma unroll
     for (int m = 0; m <= K; ++m) {
       int x = m <= last ? x0 + m * step : 0;
@@ -244,7 +272,13 @@ __device__ __forceinline__ bool run_bwd_scan_row(const BwdDesc& g, unsigned long
 #pragma unroll
     for (int m = 0; m <= K; ++m) {
       ain[m] = nA[m];
-      rec[m] = m <= nlast ? nR[m] : 0;
+      int r = nR[m];
+      if (SCANC && m > 0) {
+        const int lo = (m - 1) & 15, hi = (K - m) & 15;  // byte of row m, ascending or descending
+        const unsigned wd = up ? nRw[lo >> 2] >> (8 * (lo & 3)) : nRw[hi >> 2] >> (8 * (hi & 3));
+        r = nfull ? (int)(wd & 0xffu) : r;
+      }
+      rec[m] = m <= nlast ? r : 0;
     }
     float a = 0.0f;
     int fail = 0;
@@ -281,9 +315,22 @@ __device__ __forceinline__ bool run_bwd_scan_row(const BwdDesc& g, unsigned long
     if (cur.in && e == 0) {
       unsigned long long* xout = xbuf + (size_t)(c & 1) * ntiles * TQ + (size_t)cur.tile * TQ;
       st64_relaxed(xout + own, ((unsigned long long)(epoch_in + 1u) << 32) | __float_as_uint(a));
+      if (SCANC && kk == K) {
+        const int x1 = xof(cur, 1), xk = up ? x1 : x1 - (K - 1);
 #pragma unroll
-      for (int i = 0; i < K; ++i)
-        if (i < kk) gAout[xof(cur, i + 1)] = res[i];
+        for (int m = 0; m < K; m += 4) {
+          float4_a4 v;
+          v.x = up ? res[m] : res[K - 1 - m];
+          v.y = up ? res[m + 1] : res[K - 2 - m];
+          v.z = up ? res[m + 2] : res[K - 3 - m];
+          v.w = up ? res[m + 3] : res[K - 4 - m];
+          *(gmem<float4_a4>)(gAout + xk + m) = v;
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+          if (i < kk) gAout[xof(cur, i + 1)] = res[i];
+      }
     }
     cur = nxt;
   }

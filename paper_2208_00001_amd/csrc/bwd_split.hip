@@ -16,10 +16,11 @@ __global__ __launch_bounds__(Geo::NTCAP) void bwd_scan_cell_kernel(BwdDesc g, un
   run_bwd_scan_cell<Geo>(g, g.xbuf, words, limit, pair, &fail, xcd_remap(blockIdx.x, gridDim.x), gridDim.x);
 }
 
+template <bool SCANC>
 __global__ __launch_bounds__(kRowLanes) void bwd_scan_row_kernel(BwdDesc g, unsigned* words,
                                                                  unsigned long long limit) {
   if (ld_relaxed(words + kWordAbort) != 0u) return;
-  run_bwd_scan_row(g, g.xbuf, words, limit, xcd_remap(blockIdx.x, gridDim.x), gridDim.x);
+  run_bwd_scan_row<SCANC>(g, g.xbuf, words, limit, xcd_remap(blockIdx.x, gridDim.x), gridDim.x);
 }
 
 // One voxel per thread, threads along the contiguous axis.  A voxel's children
@@ -168,6 +169,17 @@ hipError_t launch_scan_cell(const BwdDesc& d, unsigned* words, unsigned long lon
   return hipGetLastError();
 }
 
+template <bool SCANC>
+hipError_t launch_scan_row(const BwdDesc& d, unsigned* words, unsigned long long limit, hipStream_t stream) {
+  static int cached = 0;
+  int cap = cached;
+  if (cap <= 0) cached = cap = scan_capacity(bwd_scan_row_kernel<SCANC>, kRowLanes);
+  if (cap <= 0) return hipErrorInvalidConfiguration;
+  const int grid = d.ntq < cap ? d.ntq : cap;
+  hipLaunchKernelGGL(bwd_scan_row_kernel<SCANC>, dim3(grid), dim3(kRowLanes), 0, stream, d, words, limit);
+  return hipGetLastError();
+}
+
 template <int ND>
 hipError_t launch_edges(const BwdDesc& g, const EdgeDesc& s, const unsigned* words, hipStream_t stream) {
   const long long rows = (long long)(g.N / s.d2);
@@ -191,13 +203,8 @@ hipError_t launch_bwd_scan(const BwdDesc& d, int ndim, unsigned* words, unsigned
     return hipErrorInvalidConfiguration;
   }
   if (d.TP != 1 || d.TQ != kRowTQ || d.K != kRowK) return hipErrorInvalidConfiguration;
-  static int cached = 0;
-  int cap = cached;
-  if (cap <= 0) cached = cap = scan_capacity(bwd_scan_row_kernel, kRowLanes);
-  if (cap <= 0) return hipErrorInvalidConfiguration;
-  const int grid = d.ntq < cap ? d.ntq : cap;
-  hipLaunchKernelGGL(bwd_scan_row_kernel, dim3(grid), dim3(kRowLanes), 0, stream, d, words, spin_limit);
-  return hipGetLastError();
+  return d.sa == 1 ? launch_scan_row<true>(d, words, spin_limit, stream)
+                   : launch_scan_row<false>(d, words, spin_limit, stream);
 }
 
 hipError_t launch_bwd_edges(const BwdDesc& g, int ndim, const EdgeDesc& s, const unsigned* words, hipStream_t stream) {
