@@ -215,13 +215,8 @@ int pass_chunk_for(int ndim, int C, bool scan_contiguous) {
 hipError_t launch_pass(const PassDesc& d, int ndim, unsigned* words, unsigned long long spin_limit,
                        hipStream_t stream, const PassSet* sides) {
   PassSet set{};
-  if (sides) {
-    set = *sides;
-  } else {
-    set.n = 1;
-    set.mask[0] = d.mask;
-    set.D[0] = d.D;
-  }
+  set.n = 1;
+  if (sides) set = *sides;
   // workgroups of each transform: all of them resident together
   auto grid_of = [&](int tiles, int cap) { return set.n * (tiles * set.n <= cap ? tiles : cap / set.n); };
   if (use_row_path(d, ndim)) {

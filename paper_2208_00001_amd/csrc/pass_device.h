@@ -49,6 +49,8 @@ __device__ __forceinline__ int xcd_remap(int b, int G) {
 // and returns the workgroup's number among the transform's *G workgroups.
 __device__ __forceinline__ int pick_transform(PassDesc* g, const PassSet& set, int* G) {
   const int b = xcd_remap(blockIdx.x, gridDim.x);
+  *G = (int)gridDim.x;
+  if (set.n == 1) return b;  // the descriptor's own arrays
   *G = (int)gridDim.x / set.n;
   const int i = b / *G;
   g->mask = set.mask[i];
@@ -111,10 +113,11 @@ __device__ __forceinline__ void st64_relaxed(unsigned long long* p, unsigned lon
 __device__ __forceinline__ float wait_word(const unsigned long long* a, unsigned epoch, unsigned* words,
                                            unsigned long long limit, int* fail) {
   unsigned long long wv = ld64_relaxed(a);
-  unsigned long long polls = 0;
-  while ((unsigned)(wv >> 32) != epoch) {
+  const unsigned most = limit < 0x7fffffffull ? (unsigned)limit : 0x7fffffffu;
+  unsigned polls = 0;
+  while (__builtin_expect((unsigned)(wv >> 32) != epoch, 0)) {
     ++polls;
-    if (polls > limit) {
+    if (polls > most) {
       __hip_atomic_fetch_or(words + kWordAbort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       *fail = 1;
       break;
