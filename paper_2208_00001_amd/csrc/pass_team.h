@@ -13,6 +13,8 @@
 #include "pass_cell.h"
 #include "pass_row.h"
 
+#include <type_traits>
+
 namespace ggdt {
 namespace dev {
 
@@ -24,6 +26,15 @@ constexpr int team_chunk(int K) { return K * 3 * kRowLanes; }
 // axis).
 typedef float float4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef unsigned uint4_a1 __attribute__((ext_vector_type(4), aligned(1)));
+
+// Element of a row at `lane_bytes` from its start: a wave-uniform base and a
+// 32-bit lane offset, which is one addition on the scalar unit and the access
+// itself where a per-lane index costs five instructions.
+template <class T>
+__device__ __forceinline__ gmem<T> in_row(gmem<T> row, unsigned lane_bytes) {
+  using B = std::conditional_t<std::is_const<T>::value, const char, char>;
+  return (gmem<T>)((gmem<B>)row + lane_bytes);
+}
 
 // One 2D pass by workgroup `wg` of G, each of NTEAM teams (kTeamThreads threads
 // a team).  `costs`: two chunks per team in LDS; `failw`: one LDS word.  False
@@ -94,6 +105,11 @@ __device__ __forceinline__ bool run_pass_team(const PassDesc* gp, unsigned long 
     return (g.sign > 0 ? t : Na - 1 - t) * g.sa + it.xq;
   };
   const int rstep = g.sign * g.sa;
+  // memory index of row j's first element (uniform)
+  auto row_of = [&](const Item& it, int j) {
+    const int t = it.t0 - 1 + j;
+    return (long long)(g.sign > 0 ? t : Na - 1 - t) * g.sa;
+  };
 
   if (wave != 0) {
     // Producer: rows r0 .. r0 + NR - 1 of every chunk (the last producer's rows
@@ -127,6 +143,16 @@ __device__ __forceinline__ bool run_pass_team(const PassDesc* gp, unsigned long 
           }
           return;
         }
+      }
+      if constexpr (!SCANC) {  // along the rows' axis: q is the memory column
+        const unsigned lb = it.in ? (unsigned)it.q * (unsigned)sizeof(T) : 0u;
+#pragma unroll
+        for (int j = 0; j <= NR; ++j) {
+          const long long r = row_of(it, min(r0 + j, it.kk));
+#pragma unroll
+          for (int c = 0; c < NCH; ++c) nx[j][c] = *in_row(gImage + (c * cstride + r), lb);
+        }
+        return;
       }
 #pragma unroll
       for (int j = 0; j <= NR; ++j) {
@@ -188,6 +214,13 @@ __device__ __forceinline__ bool run_pass_team(const PassDesc* gp, unsigned long 
         }
         return;
       }
+    }
+    if constexpr (!SCANC) {
+      // every row of the chunk, needed or not: a cell outside the cone uses none
+      const unsigned lb = it.in ? (unsigned)it.q * 4u : 0u;
+#pragma unroll
+      for (int j = 0; j <= K; ++j) nd[j] = *in_row(dsrc0 + row_of(it, min(j, it.kk)), lb);
+      return;
     }
     const int last = it.in ? it.kk - e : -1;  // the lane needs rows 0 .. last
 #pragma unroll
@@ -267,8 +300,6 @@ __device__ __forceinline__ bool run_pass_team(const PassDesc* gp, unsigned long 
             v.w = up ? res[m + 3] : res[K - 4 - m];
             *(gmem<float4_a4>)(gD + xk + m) = v;
           }
-#pragma unroll
-          for (int i = 0; i < K; ++i) chg |= res[i] < dd[i + 1];
           if (REC && g.rec) {
             unsigned w[4];
 #pragma unroll
@@ -287,12 +318,22 @@ __device__ __forceinline__ bool run_pass_team(const PassDesc* gp, unsigned long 
 #pragma unroll
         for (int i = 0; i < K; ++i) {
           if (i < kk) {
-            const int x = xof(cur, i + 1);
-            chg |= res[i] < dd[i + 1];
-            gD[x] = res[i];
-            if (REC && g.rec) gRec[x] = (uint8_t)rch[i];
+            if constexpr (SCANC) {
+              const int x = xof(cur, i + 1);
+              gD[x] = res[i];
+              if (REC && g.rec) gRec[x] = (uint8_t)rch[i];
+            } else {
+              const long long r = row_of(cur, i + 1);
+              *in_row(gD + r, (unsigned)cur.q * 4u) = res[i];
+              if (REC && g.rec) *in_row(gRec + r, (unsigned)cur.q) = (uint8_t)rch[i];
+            }
           }
         }
+      }
+      if (g.converge) {
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+          if (i < kk) chg |= res[i] < dd[i + 1];
       }
     }
     step_barrier();
