@@ -6,6 +6,8 @@
 #include "grid_sync.h"
 #include "layout.h"
 
+#include <type_traits>
+
 namespace ggdt {
 namespace {
 
@@ -61,13 +63,15 @@ __device__ __attribute__((noinline)) void run_bwd_layout_op_call(const BwdDesc* 
   run_bwd_layout_op(gp, ws, lds, wg, G);
 }
 
-template <bool CELL3D>
+// Geo: the tile of the thread-per-cell reverse pass (class 0); void: class 1.
+template <class Geo>
 __global__ __launch_bounds__(kCellThreads) void batched_bwd_kernel(const BatchInst* __restrict__ insts, int ninst,
                                                                const BwdDesc* __restrict__ passes, unsigned char* ws,
                                                                unsigned long long limit) {
   // The dynamic area is placed after the static LDS variables (the pass
   // barrier's flag): without the alignment it would start 4 bytes in, and every
   // 8- or 16-byte LDS access of the pass would be misaligned.
+  constexpr bool CELL3D = !std::is_void<Geo>::value;
   extern __shared__ __align__(16) float lds[];
   unsigned* words = reinterpret_cast<unsigned*>(ws);
   if (ld_relaxed(words + kWordAbort) != 0u) return;
@@ -98,7 +102,7 @@ __global__ __launch_bounds__(kCellThreads) void batched_bwd_kernel(const BatchIn
     constexpr int NT = kCellThreads;
     bool ok;
     if constexpr (CELL3D) {
-      ok = run_bwd_pass_cell_mode(gp, xbuf, words, cls, limit, lds, wg, in.nwg);
+      ok = run_bwd_pass_cell_mode<Geo>(gp, xbuf, words, cls, limit, lds, wg, in.nwg);
     } else if (in.ndim == 3) {
       ok = scanc ? run_bwd_pass_mode<3, kTP3, kTQ3, kBwdBatchK3, true, NT>(gp, xbuf, words, cls, limit, lds, wg, in.nwg)
                  : run_bwd_pass_mode<3, kTP3, kTQ3, kBwdBatchK3, false, NT>(gp, xbuf, words, cls, limit, lds, wg, in.nwg);
@@ -131,19 +135,23 @@ size_t batched_bwd_lds_bytes(int c2, int c3) {
   return b;
 }
 
-int batched_bwd_capacity(int bclass, size_t lds) {
-  return capacity_of(bclass == 0 ? (const void*)batched_bwd_kernel<true> : (const void*)batched_bwd_kernel<false>,
-                     lds, kCellThreads);
+using BatchedBwdKernel = void (*)(const BatchInst*, int, const BwdDesc*, unsigned char*, unsigned long long);
+
+static BatchedBwdKernel pick_bwd(int bclass, int TP, int TQ) {
+  if (bclass != 0) return batched_bwd_kernel<void>;
+  if (TP == 16) return batched_bwd_kernel<CellGeomBase>;
+  return TQ == 16 ? batched_bwd_kernel<CellGeomMid> : batched_bwd_kernel<CellGeomSmall>;
 }
 
-hipError_t launch_batched_bwd(int bclass, const BatchInst* insts, int ninst, const BwdDesc* passes, unsigned char* ws,
-                              int grid, size_t lds, unsigned long long spin_limit, hipStream_t stream) {
-  if (bclass == 0)
-    hipLaunchKernelGGL(batched_bwd_kernel<true>, dim3(grid), dim3(kCellThreads), lds, stream, insts, ninst, passes,
-                       ws, spin_limit);
-  else
-    hipLaunchKernelGGL(batched_bwd_kernel<false>, dim3(grid), dim3(kCellThreads), lds, stream, insts, ninst, passes,
-                       ws, spin_limit);
+int batched_bwd_capacity(int bclass, int TP, int TQ, size_t lds) {
+  return capacity_of((const void*)pick_bwd(bclass, TP, TQ), lds, kCellThreads);
+}
+
+hipError_t launch_batched_bwd(int bclass, int TP, int TQ, const BatchInst* insts, int ninst, const BwdDesc* passes,
+                              unsigned char* ws, int grid, size_t lds, unsigned long long spin_limit,
+                              hipStream_t stream) {
+  hipLaunchKernelGGL(pick_bwd(bclass, TP, TQ), dim3(grid), dim3(kCellThreads), lds, stream, insts, ninst, passes, ws,
+                     spin_limit);
   return hipGetLastError();
 }
 

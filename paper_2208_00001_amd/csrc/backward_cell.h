@@ -7,7 +7,7 @@
 //   Ibar(y) -= coef(x_j) * (I(x_j) - I(y)) for the same children, j ascending
 //   Ibar(y) += coef(y) * (I(y) - I(y'))     when y has a parent y'
 //   abar_out(y) = record(y) ? 0 : abar(y)
-// with the same overlapped tiling: 16 x 16 tiles, chunks of K = 8 planes, a
+// with the same overlapped tiling: tiles of up to 16 x 16, chunks of K = 8 planes, a
 // halo shrinking by one voxel per plane, and epoch-tagged exchange words for the
 // chunk's last parent plane.  A workgroup of 1024 threads covers the tile's
 // 32 x 32 box, one thread per cell for the whole pass.  A thread keeps its
@@ -52,10 +52,13 @@ __device__ __forceinline__ float bwd_cell_edge_rt(const BwdDesc& g, int j, float
   return general_root<MODE, false>(fmaf(g.lam, d * d, spatial_term(g, j)));
 }
 
-template <int MODE>
+// Geo: the tile (16 x 16, or smaller where a batch's tiles then still have a CU
+// each); threads past a smaller tile's box lie further out than K and only
+// meet the barriers.
+template <int MODE, class Geo>
 __device__ __forceinline__ bool run_bwd_pass_cell(const BwdDesc* gp, unsigned long long* xbuf, unsigned* words,
                                                   unsigned long long limit, float* lds, int wg, int G) {
-  constexpr int TP = kCellTP, TQ = kCellTQ, K = kCellK, BQ = kCellBQ, NB = kCellThreads;
+  constexpr int TP = Geo::TP, TQ = Geo::TQ, K = Geo::K, BQ = Geo::BQ, NB = kCellThreads;
   BwdDesc g = *gp;
   if (g.a_in_off >= 0) g.a_in = reinterpret_cast<const float*>(reinterpret_cast<unsigned char*>(words) + g.a_in_off);
   if (g.a_out_off >= 0) g.a_out = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(words) + g.a_out_off);
@@ -330,16 +333,17 @@ __device__ __forceinline__ bool run_bwd_pass_cell(const BwdDesc* gp, unsigned lo
   return true;
 }
 
+template <class Geo>
 __device__ __forceinline__ bool run_bwd_pass_cell_mode(const BwdDesc* gp, unsigned long long* xbuf, unsigned* words,
                                                        const unsigned* cls_word, unsigned long long limit,
                                                        float* lds, int wg, int G) {
   const int mode = gp->mode;
-  if (mode == kModeLam0) return run_bwd_pass_cell<kModeLam0>(gp, xbuf, words, limit, lds, wg, G);
+  if (mode == kModeLam0) return run_bwd_pass_cell<kModeLam0, Geo>(gp, xbuf, words, limit, lds, wg, G);
   if (mode == kModeLam1C1 && fast_mode_ok(kModeLam1C1, ld_relaxed(cls_word)))
-    return run_bwd_pass_cell<kModeLam1C1>(gp, xbuf, words, limit, lds, wg, G);
+    return run_bwd_pass_cell<kModeLam1C1, Geo>(gp, xbuf, words, limit, lds, wg, G);
   if (mode == kModeGeneral && general_n_ok(gp->sqrt_normal, cls_word))
-    return run_bwd_pass_cell<kModeGeneralN>(gp, xbuf, words, limit, lds, wg, G);
-  return run_bwd_pass_cell<kModeGeneral>(gp, xbuf, words, limit, lds, wg, G);
+    return run_bwd_pass_cell<kModeGeneralN, Geo>(gp, xbuf, words, limit, lds, wg, G);
+  return run_bwd_pass_cell<kModeGeneral, Geo>(gp, xbuf, words, limit, lds, wg, G);
 }
 
 }  // namespace dev

@@ -27,6 +27,7 @@ struct ggdt_plan {
   // backward tables (when every instance has records and gradient buffers)
   bool has_bwd = false;
   int bclass = 0;
+  int btp = 16, btq = 16;  // its volume tile
   int bgrid = 0;
   size_t blds = 0;
   size_t fwd_ws = 0;
@@ -371,7 +372,11 @@ int ggdt_batched_plan(const ggdt_instance* instances, int n, const ggdt_tuning* 
     // (single-channel volumes: room for four tiles of the layout changes)
     const size_t blds0 = batched_bwd_lds_bytes(maxC2, maxC3), lds4 = (size_t)4 * 64 * 65 * 4;
     const size_t blds = bclass == 0 && blds0 < lds4 ? lds4 : blds0;
-    int bcap = blds <= kMaxLdsBytes ? batched_bwd_capacity(bclass, blds) : 0;
+    // class 0: the smaller tiles where every tile still has a CU, as in the forward
+    const int small = bclass == 0 ? untuned_class(prs) : 0;
+    const int btp = small == 3 || small == 4 ? kBatchTP3[small] : kTP3;
+    const int btq = small == 3 || small == 4 ? kBatchTQ3[small] : kTQ3;
+    int bcap = blds <= kMaxLdsBytes ? batched_bwd_capacity(bclass, btp, btq, blds) : 0;
     if (tuning && tuning->wg_per_cu > 0 && bcap > 0) {
       int dev = 0, cus = 0;
       if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess)
@@ -441,6 +446,12 @@ int ggdt_batched_plan(const ggdt_instance* instances, int n, const ggdt_tuning* 
           if (rc) {
             ggdt_plan_destroy(plan);
             return rc;
+          }
+          if (bclass == 0) {
+            d.TP = btp;
+            d.TQ = btq;
+            d.ntp = (d.Np + btp - 1) / btp;
+            d.ntq = (d.Nq + btq - 1) / btq;
           }
           base += (unsigned)d.nchunk + 1u;
           // abar_in: grad_out, then the previous reversed pass's output; outputs
@@ -530,6 +541,8 @@ int ggdt_batched_plan(const ggdt_instance* instances, int n, const ggdt_tuning* 
       }
       plan->has_bwd = true;
       plan->bclass = bclass;
+      plan->btp = btp;
+      plan->btq = btq;
       plan->bgrid = bwg0;
       plan->blds = blds;
     }
@@ -588,8 +601,8 @@ int ggdt_batched_backward(const ggdt_plan* plan, void* workspace, size_t workspa
       return GGDT_ERR_HIP;
   }
   prof_before(stream);
-  const hipError_t e = launch_batched_bwd(plan->bclass, plan->d_binsts, plan->n, plan->d_bpasses, ws, plan->bgrid,
-                                          plan->blds, g_spin_limit, stream);
+  const hipError_t e = launch_batched_bwd(plan->bclass, plan->btp, plan->btq, plan->d_binsts, plan->n,
+                                          plan->d_bpasses, ws, plan->bgrid, plan->blds, g_spin_limit, stream);
   prof_after(stream);
   if (e != hipSuccess) return GGDT_ERR_HIP;
   for (int i = 0; i < plan->n; ++i) {

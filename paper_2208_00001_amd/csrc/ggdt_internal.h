@@ -174,7 +174,7 @@ struct BatchInst {
 
 // Tile geometry of the batched kernels (3D plane tile TP3 x TQ3, 2D row tile TQ2).
 constexpr int kTP3 = 16, kTQ3 = 16, kTQ2 = 256;
-// 2D row kernel (pass_row.h): one 64-lane wave per tile, chunks of kRowK rows,
+// 2D passes (pass_team.h): 64 lanes per tile, chunks of kRowK rows,
 // kRowTQ = 64 - 2 kRowK owned cells per tile, images of up to kRowMaxC channels.
 constexpr int kRowLanes = 64, kRowK = 16, kRowTQ = kRowLanes - 2 * kRowK, kRowMaxC = 3;
 
@@ -222,9 +222,10 @@ hipError_t launch_bwd_edges(const BwdDesc& g, int ndim, const EdgeDesc& s, const
 size_t batched_bwd_lds_bytes(int c2, int c3);
 // Batched reverse kernel class: 0 when every instance is a single-channel volume
 // (thread-per-cell reverse pass), else 1 (tile reverse passes).
-int batched_bwd_capacity(int bclass, size_t lds);
-hipError_t launch_batched_bwd(int bclass, const BatchInst* insts, int ninst, const BwdDesc* passes, unsigned char* ws,
-                              int grid, size_t lds, unsigned long long spin_limit, hipStream_t stream);
+int batched_bwd_capacity(int bclass, int TP, int TQ, size_t lds);  // TP, TQ: class 0's volume tile
+hipError_t launch_batched_bwd(int bclass, int TP, int TQ, const BatchInst* insts, int ninst, const BwdDesc* passes,
+                              unsigned char* ws, int grid, size_t lds, unsigned long long spin_limit,
+                              hipStream_t stream);
 // Chunk lengths of the batched backward kernel.
 constexpr int kBwdBatchK3 = 4, kBwdBatchK2 = 16;
 // Chunk length of single-channel 3D instances in batched reverse passes (the

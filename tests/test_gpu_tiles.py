@@ -150,3 +150,23 @@ def test_toivanen_row_ends(shape, C, lam):
     args = (c["spacing"], c["v"], c["lam"], 2)
     ref = oracle.toivanen(c["image"], c["mask"], *args, "f32")
     same(to_host(B.ggdt_toivanen(to_dev(c["image"]), to_dev(c["mask"]), *args, check=True)), ref, c["name"])
+
+
+@pytest.mark.parametrize("shapes", [[(9, 70, 60), (12, 33, 41)], [(9, 130, 190)], [(9, 160, 200), (10, 150, 180)]], ids=str)
+@pytest.mark.parametrize("lam", [0.0, 0.7, 1.0])
+def test_batched_reverse_tile_sizes(shapes, lam):
+    """Batches of volumes whose reverse takes 8 x 8, 8 x 16 and 16 x 16 tiles."""
+    from paper_2208_00001_amd.batched import BatchedPlan
+    cs = [synth.small_case(s, C=1, seed=85 + i, lam=lam, iterations=1, soft=True, v=10.0) for i, s in enumerate(shapes)]
+    W = [np.random.default_rng(86 + i).standard_normal(s).astype(np.float32) for i, s in enumerate(shapes)]
+    plan = BatchedPlan([dict(image=to_dev(c["image"]), softmask=to_dev(c["mask"]), spacing=c["spacing"], v=c["v"],
+                             lam=c["lam"], iterations=1, records=True, grad_out=to_dev(w)) for c, w in zip(cs, W)])
+    plan.run()
+    grads = plan.backward()
+    plan.check()
+    for c, w, (gi, gm) in zip(cs, W, grads):
+        _, rrec = oracle.ggdt(c["image"], c["mask"], c["spacing"], c["v"], c["lam"], 1, "f32", records=True)
+        rgi, rgm = oracle.backward(c["image"], rrec, w, c["spacing"], c["v"], c["lam"], 1, "f32")
+        same(to_host(gm), rgm, "dL/dM")
+        same(to_host(gi), rgi, "dL/dI")
+    plan.close()
