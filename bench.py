@@ -57,7 +57,8 @@ PMC_SUMMARY = os.path.join(ROOT, "profiles", "pass_kernel_3d_256_pmc.json")
 # Sources that define and launch the forward pass kernels and the scale kernel
 # the counters are calibrated with: a change to any of them makes the stored
 # counter summary stale.
-PASS_KERNEL_SOURCES = ("forward.hip", "ggdt_internal.h", "pass_cell.h", "pass_device.h")
+PASS_KERNEL_SOURCES = ("cell_base.hip", "cell_kernels.h", "forward.hip", "ggdt_internal.h", "pass_cell.h",
+                       "pass_device.h")
 
 
 def kernel_source_digest() -> str:

@@ -70,14 +70,14 @@ const char* ggdt_strerror(int status);
  * `dims` (array-axis order) and C channels.  Returns 0 for invalid shapes.  The
  * workspace holds inter-workgroup progress flags, the image classification
  * word and the watchdog word; its content need not be initialised by the
- * caller.  For single-channel volumes it also holds copies of D and of the
+ * caller.  For volumes of up to 3 channels it also holds copies of D and of the
  * image laid out [W][D][H] (the last axis slowest), on which the passes along
  * the last axis run as strided passes, and room for one such pass's records
  * before they are moved to the array layout (a library addition; the passes
  * compute the same values and records).  ggdt_workspace_min_bytes is the smallest size the
  * forward accepts: with less than ggdt_workspace_bytes it runs those passes in
- * place, more slowly.  The two are equal for images and multi-channel
- * volumes. */
+ * place, more slowly.  The two are equal for images and for volumes of more
+ * channels. */
 size_t ggdt_workspace_bytes(int ndim, const int* dims, int C);
 size_t ggdt_workspace_min_bytes(int ndim, const int* dims, int C);
 
@@ -172,9 +172,8 @@ int ggdt_workspace_iterations(const void* workspace, hipStream_t stream, int* it
 
 /* Bytes of device workspace the backward entry points use: the forward's
  * minimal workspace plus one fp32 adjoint buffer of prod(dims) values, plus,
- * for single-channel volumes, scan-major copies (image, two adjoint volumes,
- * dL/dI, two passes' records) on which the reverses of the passes along the
- * last axis run as strided passes.  ggdt_backward_workspace_min_bytes is the
+ * for volumes, scan-major copies (two adjoint volumes, a pass's records) on
+ * which the reverses of the passes along the last axis run as strided passes.  ggdt_backward_workspace_min_bytes is the
  * smallest size accepted (without the copies those reverse passes run in
  * place, more slowly).  0 for invalid shapes.  1 <= C <= 8 for the backward. */
 size_t ggdt_backward_workspace_bytes(int ndim, const int* dims, int C);
@@ -213,10 +212,13 @@ int ggdt3d_backward(const float* image, const uint8_t* records, const float* gra
  * workspace.  theta_d, theta_e must be finite and >= 0 (else
  * GGDT_ERR_BAD_PARAM). */
 
-/* Workspace bytes: the transform's minimal workspace plus 2 (signed) or 4
- * (GSF) fp32 buffers of prod(dims) values, plus, for single-channel volumes,
- * the scan-major area described at ggdt_workspace_bytes (with less room, the
- * passes along the last axis run in place).  0 for invalid shapes. */
+/* Workspace bytes for the transforms of one image to run side by side where
+ * that is faster (images, smaller volumes): their exchange words, 2 (signed) or 7
+ * (GSF) fp32 buffers of prod(dims) values and their scan-major copies.  With
+ * less room, and at least the transform's minimal workspace plus 2 (signed) or
+ * 4 (GSF) buffers, they run one after the other (the passes along a volume's
+ * last axis in place without a further scan-major area as described at
+ * ggdt_workspace_bytes).  0 for invalid shapes. */
 size_t ggdt_signed_workspace_bytes(int ndim, const int* dims, int C);
 size_t ggdt_gsf_workspace_bytes(int ndim, const int* dims, int C);
 
@@ -335,11 +337,11 @@ typedef struct ggdt_plan ggdt_plan;
  * until ggdt_plan_destroy.  Errors are those of the plain entries, for the first
  * offending instance. */
 typedef struct ggdt_tuning {
-  int tile_p;      /* 3D plane tile side: 0 or 16 (default), or 24 (single-channel batches only; 24 x 24
+  int tile_p;      /* 3D plane tile side: 0 (chosen by the plan), 16, or 24 (single-channel batches only; 24 x 24
                       tiles with chunk 4: less halo arithmetic for more exchanges); other values
                       GGDT_ERR_BAD_PARAM */
   int tile_q;      /* same as tile_p (either selects the side) */
-  int chunk;       /* scan steps between inter-workgroup syncs: 0 (default), 8 or 32 (single-channel
+  int chunk;       /* scan steps between inter-workgroup syncs: 0 (chosen by the plan), 8 or 32 (single-channel
                       kernels), 4 or 16 (kernels for up to 4 channels); 0 or 4 with tile side 24 */
   int wg_per_cu;   /* resident workgroups per compute unit to plan for (0 = default) */
 } ggdt_tuning;

@@ -142,7 +142,7 @@ def workspace_bytes(spatial: Sequence[int], C: int) -> int:
 
 
 def workspace_min_bytes(spatial: Sequence[int], C: int) -> int:
-    """Smallest forward workspace: single-channel volumes then run the passes
+    """Smallest forward workspace: volumes of up to 3 channels then run the passes
     along the last axis in place instead of on scan-major copies."""
     lib = load_library()
     return int(lib.ggdt_workspace_min_bytes(len(spatial), _dims(spatial), C))

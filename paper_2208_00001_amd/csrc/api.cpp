@@ -254,8 +254,8 @@ static hipError_t image_to_scan_major(const Problem& pr, const void* image, cons
   return hipSuccess;
 }
 
-// 2D passes of images with up to kRowMaxC channels run on the row kernel
-// (one wave per 32-cell tile, chunks of 16 rows).  Its exchange area,
+// 2D passes of images with up to kRowMaxC channels run on the team kernel
+// (32-cell tiles, chunks of 16 rows).  Its exchange area,
 // ceil(Nq / 32) * 32 words per parity, fits in the tile kernel's.
 static void use_row_geometry(const Problem& pr, PassDesc* d) {
   if (pr.ndim != 2 || pr.C > kRowMaxC) return;

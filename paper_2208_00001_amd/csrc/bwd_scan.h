@@ -217,7 +217,7 @@ __device__ __forceinline__ bool run_bwd_scan_row(const BwdDesc& g, unsigned long
     const int t = it.T0 - m;
     return (g.sign > 0 ? t : Na - 1 - t) * g.sa + it.xq;
   };
-  // Branch-free loads, as in the forward row pass: an unneeded row is read from
+  // Branch-free loads, as in the team pass: an unneeded row is read from
   // a clamped, in-bounds address and dropped where consumed.
   float nA[K + 1];
   int nR[K + 1];

@@ -241,7 +241,7 @@ hipError_t launch_pass(const PassDesc& d, int ndim, unsigned* words, unsigned lo
                        spin_limit);
     return hipGetLastError();
   }
-  if (d.img_fmt != kImgF32) return hipErrorInvalidConfiguration;  // 16-bit images: cell and row kernels only
+  if (d.img_fmt != kImgF32) return hipErrorInvalidConfiguration;  // 16-bit images: cell and team kernels only
   PassKernel fn = select_kernel(d, ndim);
   if (!fn) return hipErrorInvalidConfiguration;
   const size_t lds = lds_bytes_for(ndim, d.K, d.C, d.sa == 1);

@@ -1,5 +1,5 @@
 // Device code of one 3D directional pass with one thread per cell of the tile
-// box (single-channel images).
+// box (images of up to three channels).
 //
 // Same decomposition as run_pass in pass_device.h: the plane is cut into tiles
 // owned by workgroups, the scan axis into chunks of K = 8 steps, and each chunk
@@ -75,11 +75,6 @@ __device__ __forceinline__ float cell_edge(const PassDesc& g, int j, const float
   return general_root<MODE, (NCH > 1)>(fmaf(g.lam, s, g.A[j]));
 }
 
-// One pass of one single-channel 3D instance by workgroup `wg` of G (blockDim
-// = 1024), `lds` laid out as cell_lds_bytes(SCANC) describes.  SCANC: the scan
-// axis is the contiguous memory axis; a thread's planes are then consecutive
-// floats, and are gathered through LDS by 16-byte runs instead of one load per
-// lane and plane.  False if a bounded wait gave up.
 // Workgroup barrier for the step loop: this wave's LDS accesses are complete
 // (lgkmcnt(0)) and the compiler moves no memory access across it.  Unlike a
 // release fence it does not wait for global stores or for global->LDS copies
@@ -111,6 +106,10 @@ __device__ __forceinline__ CellLds carve_cell_lds(float* lds) {
                  reinterpret_cast<int*>(lds + 4 * kCellThreads)};
 }
 
+// One pass of one 3D instance of NCH channels by workgroup `wg` of G.  SCANC: the
+// scan axis is the contiguous memory axis; a thread's planes are then consecutive
+// floats, and are gathered through LDS by 16-byte runs instead of one load per
+// lane and plane.  False if a bounded wait gave up.
 template <bool SCANC, int MODE, bool REC, class Geo = CellGeomBase, int FMT = kImgF32, int NCH = 1>
 __device__ __forceinline__ bool run_pass_cell(const PassDesc* gp, unsigned long long* xbuf, unsigned* words,
                                               unsigned long long limit, const CellLds& lds, int wg, int G) {
