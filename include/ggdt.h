@@ -172,8 +172,10 @@ int ggdt_workspace_iterations(const void* workspace, hipStream_t stream, int* it
 
 /* Bytes of device workspace the backward entry points use: the forward's
  * minimal workspace plus one fp32 adjoint buffer of prod(dims) values, plus,
- * for volumes, scan-major copies (two adjoint volumes, a pass's records) on
- * which the reverses of the passes along the last axis run as strided passes.  ggdt_backward_workspace_min_bytes is the
+ * for volumes, scan-major copies (two adjoint volumes, a pass's records; for large
+ * single-channel volumes also the image, dL/dI and another pass's records) on
+ * which the reverses of the passes along the last axis run as strided passes.
+ * ggdt_backward_workspace_min_bytes is the
  * smallest size accepted (without the copies those reverse passes run in
  * place, more slowly).  0 for invalid shapes.  1 <= C <= 8 for the backward. */
 size_t ggdt_backward_workspace_bytes(int ndim, const int* dims, int C);

@@ -1,6 +1,6 @@
-// Batched backward (reverse-mode) kernels: one persistent launch over many
-// instances (see backward_device.h; the single-instance reverse is in
-// bwd_split.hip).
+// Backward (reverse-mode) kernels: the batched persistent launch over many
+// instances (see backward_device.h), and the thread-per-cell reverse pass of one
+// large volume (smaller volumes, images and channels: bwd_split.hip).
 #include "backward_cell.h"
 #include "backward_device.h"
 #include "grid_sync.h"
@@ -21,6 +21,16 @@ int capacity_of(const void* fn, size_t lds, int threads = kThreads) {
     return 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, lds) != hipSuccess) return 0;
   return per_cu * cus;
+}
+
+// One reversed pass of one single-channel volume on 16 x 16 tiles (backward_api.cpp
+// says for which).
+__global__ __launch_bounds__(kCellThreads) void bwd_pass_cell_kernel(BwdDesc g, unsigned* words,
+                                                                     unsigned long long limit) {
+  __shared__ __align__(16) float lds[(kBwdCellLdsBytes + 3) / 4];
+  if (ld_relaxed(words + kWordAbort) != 0u) return;
+  run_bwd_pass_cell_mode<CellGeomBase>(&g, g.xbuf, words, words + kWordClass, limit, lds,
+                                       xcd_remap(blockIdx.x, gridDim.x), gridDim.x);
 }
 
 // Batched: every reversed pass of every instance, instance-local barriers in
@@ -116,6 +126,17 @@ __global__ __launch_bounds__(kCellThreads) void batched_bwd_kernel(const BatchIn
 }
 
 }  // namespace
+
+hipError_t launch_bwd_pass(const BwdDesc& d, unsigned* words, unsigned long long spin_limit, hipStream_t stream) {
+  if (d.C != 1 || d.K != kCellK || d.TP != kCellTP || d.TQ != kCellTQ) return hipErrorInvalidConfiguration;
+  static int cached = 0;
+  int cap = cached;
+  if (cap <= 0) cached = cap = capacity_of((const void*)bwd_pass_cell_kernel, 0, kCellThreads);
+  if (cap <= 0) return hipErrorInvalidConfiguration;
+  const int ntiles = d.ntp * d.ntq, grid = ntiles < cap ? ntiles : cap;
+  hipLaunchKernelGGL(bwd_pass_cell_kernel, dim3(grid), dim3(kCellThreads), 0, stream, d, words, spin_limit);
+  return hipGetLastError();
+}
 
 // c2 / c3: the largest channel count of the batch's 2D / 3D instances (0: none).
 size_t batched_bwd_lds_bytes(int c2, int c3) {

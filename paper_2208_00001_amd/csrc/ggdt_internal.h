@@ -203,7 +203,10 @@ hipError_t launch_batched(int kclass, bool rec, const BatchInst* insts, int nins
                           unsigned char* ws, int grid, size_t lds, unsigned long long spin_limit, hipStream_t stream);
 hipError_t launch_batched_classify(const BatchInst* insts, int ninst, unsigned char* ws, hipStream_t stream);
 
-// Second launch of a single-instance reversed pass (bwd_split.hip): a is the
+// A single-instance reversed pass in one launch (backward.hip): single-channel
+// volumes on 16 x 16 tiles.  dL/dI is accumulated in d.gI.
+hipError_t launch_bwd_pass(const BwdDesc& d, unsigned* words, unsigned long long spin_limit, hipStream_t stream);
+// Second launch of a single-instance reversed pass in two (bwd_split.hip): a is the
 // scan's output (abar before zeroing), out the next pass's abar_in, gI the
 // image gradient.
 struct EdgeDesc {
