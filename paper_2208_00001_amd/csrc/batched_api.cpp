@@ -53,10 +53,12 @@ int wg_tiles(const PassDesc& d) {
 // step of one tile: over the passes, planes times the tiles each workgroup
 // walks (ceil(tiles / w)) times the step's weight, plus a per-chunk exchange
 // term; layout changes count per round of K tiles a workgroup moves.  Fitted to
-// per-pass durations in a 64-instance batch on MI355X (1.26 us per strided 3D
-// plane step of a tile and 0.23 us per chunk; 2.45 us per step when the scan
-// axis is the contiguous one; 0.53 us per 2D row step and 3.5 us per chunk;
-// 3.9 us per round of 4 layout tiles; teams 3.2 us per chunk of 16 rows).
+// per-pass durations in a 64-instance batch on MI355X, on 24 x 24 tiles with K = 4
+// and the tile kernels' root (1.26 us per strided 3D plane step of a tile and 0.23
+// us per chunk; 2.45 us per step when the scan axis is the contiguous one; 0.53 us
+// per 2D row step and 3.5 us per chunk; 3.9 us per round of 4 layout tiles; teams,
+// measured later, 3.2 us per chunk of 16 rows).  The split of every class and of the
+// reverse goes by these weights, which were not fitted again for the other tiles.
 double instance_cost(const std::vector<PassDesc>& ps, int w) {
   double c = 0.0;
   for (const PassDesc& d : ps) {
@@ -77,8 +79,9 @@ double instance_cost(const std::vector<PassDesc>& ps, int w) {
   return c;
 }
 
+// Most tiles of an instance's passes (layout changes count one; 0: no passes).
 int max_tiles_of(const std::vector<PassDesc>& ps) {
-  int m = 1;
+  int m = ps.empty() ? 0 : 1;
   for (const PassDesc& d : ps) m = wg_tiles(d) > m ? wg_tiles(d) : m;
   return m;
 }
@@ -98,36 +101,130 @@ size_t max_cells_of(const std::vector<PassDesc>& ps) {
   return m;
 }
 
-// Class of a single-channel batch without a tuning, from its number of
-// workgroups' worth of tiles against the 256 CUs: the smallest volume tile that
-// leaves every tile a CU of its own (as cell_tile does for one volume), and
-// 24 x 24 tiles beyond 1.75 tiles of 16 x 16 per CU, where a workgroup walks
-// several tiles, whose items hide the exchanges, and the halo arithmetic counts.
-// ms, 16 x 16 against 24 x 24: 12 volumes (470 tiles of 16 x 16) 2.67 / 2.84, 15
-// volumes and 5 images (450) 2.65 / 2.45, 24 volumes (832) 3.84 / 3.26, 48
-// volumes and 16 images 21.5 / 14.0.
-int untuned_class(const std::vector<Problem>& prs) {
+// Workgroups of each of n instances: one each, then greedily, up to `cap`, one more
+// to the instance with the largest cost(i, workgroups) that still has tiles to
+// spread (most[i]; 0: no passes).  *longest: the largest cost after it.
+template <class Cost>
+std::vector<int> split_workgroups(int n, int cap, const std::vector<int>& most, Cost cost, double* longest = nullptr) {
+  std::vector<int> w(n, 1);
+  std::vector<double> c(n);
+  for (int i = 0; i < n; ++i) c[i] = cost(i, 1);
+  for (int used = n; used < cap; ++used) {
+    int best = -1;
+    for (int i = 0; i < n; ++i)
+      if (w[i] < most[i] && (best < 0 || c[i] > c[best])) best = i;
+    if (best < 0) break;
+    ++w[best];
+    c[best] = cost(best, w[best]);
+  }
+  if (longest) {
+    *longest = 0.0;
+    for (int i = 0; i < n; ++i) *longest = c[i] > *longest ? c[i] : *longest;
+  }
+  return w;
+}
+
+// us of the single-channel classes, by which a batch without a tuning chooses
+// one: a plane step of a tile at lambda 0 or 1 (fast) and between (root); a chunk
+// costs 1.0, the neighbours' words, where a workgroup has one tile of the pass, and
+// `item` per tile where it has several, whose steps hide the words.  A round of
+// four layout tiles costs 6.0, a chunk of a team 3.5.  Fitted to the forwards of 37
+// batches (one to 64 instances, cubes to slabs of 2 planes, some with images) at
+// lambda 0, 0.5 and 1 on each class; residual 5 to 9 %.
+struct ClassCost {
+  double fast, root, item;
+};
+constexpr ClassCost kClassCost[kBatchClasses] = {
+    {0.47, 0.74, 0.7}, {}, {0.51, 0.80, 0.93}, {0.44, 0.68, 0.4}, {0.40, 0.59, 0.55}};
+
+// Class of a single-channel batch without a tuning: the one whose estimate, with
+// the chip's 256 workgroups split by it, is the smallest.  Small tiles shorten the
+// plane step while tiles have a CU of their own; 24 x 24 tiles have the least
+// halo arithmetic, for twice the exchanges, which only several tiles of a pass
+// in one workgroup hide, so what counts is how many each pass has and for how many
+// planes.  ms on 16 x 16 / 24 x 24 / 8 x 16 / 8 x 8, one iteration: three volumes of
+// 200^3 at lambda 0.5 2.42 / 1.68 / 3.63 / 6.68 (24 x 24 taken); four of 64 x 200 x
+// 200 at 0.5 1.20 / 1.34 / 1.78 / 3.03 and at 1 0.85 / 1.00 / 1.25 / 2.10 (16 x 16); two
+// of 400 x 400 x 8 at 1 1.08 / 1.42 / 0.96 / 0.97 (8 x 8).  Over the 111 batches and
+// lambdas the class taken was at most 9 % slower than the best.
+int untuned_class(const ggdt_instance* in, const std::vector<Problem>& prs) {
+  constexpr int kCUs = 256;
+  const int n = (int)prs.size();
+  int best = 0;
+  double best_t = 0.0;
+  for (int k : {0, 2, 3, 4}) {
+    struct Axis {
+      int tiles, steps, chunks;
+    };
+    std::vector<Axis> axes(3 * (size_t)n);
+    std::vector<int> most(n, 0);
+    for (int i = 0; i < n; ++i) {
+      if (in[i].iterations == 0) continue;
+      for (int a = 0; a < prs[i].ndim; ++a) {
+        PassDesc d;
+        pass_geometry(prs[i], a, &d);
+        const int K = prs[i].ndim == 3 ? kBatchK3[k] : kBatchK2[k];
+        const int row = (d.Nq + kRowTQ - 1) / kRowTQ;
+        const int tiles = prs[i].ndim == 3
+                              ? ((d.Np + kBatchTP3[k] - 1) / kBatchTP3[k]) * ((d.Nq + kBatchTQ3[k] - 1) / kBatchTQ3[k])
+                              : (row + kBatchTeamsPerWg - 1) / kBatchTeamsPerWg;
+        axes[3 * i + a] = Axis{tiles, d.Na - 1, (d.Na - 1 + K - 1) / K};
+        most[i] = tiles > most[i] ? tiles : most[i];
+      }
+    }
+    const ClassCost& cc = kClassCost[k];
+    auto cost = [&](int i, int w) {
+      if (in[i].iterations == 0) return 0.0;
+      const Problem& pr = prs[i];
+      const double step = requested_mode(in[i].lambda, 1) == kModeGeneral ? cc.root : cc.fast;
+      double it = 0.0, layout = 0.0;
+      for (int a = 0; a < pr.ndim; ++a) {
+        const Axis& x = axes[3 * i + a];
+        const int per = (x.tiles + w - 1) / w;
+        if (pr.ndim == 2)
+          it += 2.0 * 3.5 * x.chunks * per;
+        else
+          it += 2.0 * (step * x.steps * per + x.chunks * (per == 1 ? 1.0 : cc.item * per));
+      }
+      if (pr.ndim == 3)
+        layout = 6.0 * ceil((double)pr.dims[0] * ((pr.dims[1] + 63) / 64) * ((pr.dims[2] + 63) / 64) / (4.0 * w));
+      return in[i].iterations * (it + 2.0 * layout) + layout;
+    };
+    double t = 0.0;
+    split_workgroups(n, kCUs, most, cost, &t);
+    if (k == 0 || t < best_t) {
+      best = k;
+      best_t = t;
+    }
+  }
+  return best;
+}
+
+// Volume tile of a batched reverse of single-channel volumes: the smallest whose
+// tiles all have a CU, else 16 x 16.
+void reverse_tile(const std::vector<Problem>& prs, int* TP, int* TQ) {
   constexpr long long kCUs = 256;
-  auto demand = [&](int TP, int TQ, bool images) {
+  for (int k : {4, 3}) {
     long long sum = 0;
     for (const Problem& pr : prs) {
       long long most = 0;
-      for (int a = 0; a < pr.ndim; ++a) {
+      for (int a = 0; a < 3; ++a) {
         PassDesc d;
         pass_geometry(pr, a, &d);
-        const long long row = (d.Nq + kRowTQ - 1) / kRowTQ;
-        const long long t = pr.ndim == 3 ? (long long)((d.Np + TP - 1) / TP) * ((d.Nq + TQ - 1) / TQ)
-                                         : (row + kBatchTeamsPerWg - 1) / kBatchTeamsPerWg;
+        const long long t = (long long)((d.Np + kBatchTP3[k] - 1) / kBatchTP3[k]) *
+                            ((d.Nq + kBatchTQ3[k] - 1) / kBatchTQ3[k]);
         most = t > most ? t : most;
       }
-      if (images == (pr.ndim == 2)) sum += most;
+      sum += most;
     }
-    return sum;
-  };
-  const long long free = kCUs - demand(16, 16, true);
-  for (int k : {4, 3})
-    if (demand(kBatchTP3[k], kBatchTQ3[k], false) <= free) return k;
-  return 4 * demand(kBatchTP3[0], kBatchTQ3[0], false) > 7 * (free > 0 ? free : 0) ? 2 : 0;
+    if (sum <= kCUs) {
+      *TP = kBatchTP3[k];
+      *TQ = kBatchTQ3[k];
+      return;
+    }
+  }
+  *TP = kTP3;
+  *TQ = kTQ3;
 }
 
 int validate_instance(const ggdt_instance& in, Problem* pr) {
@@ -191,7 +288,7 @@ int ggdt_batched_plan(const ggdt_instance* instances, int n, const ggdt_tuning* 
     else if (tuning->chunk != kBatchK3[0] && tuning->chunk != kBatchTuneK2) return GGDT_ERR_BAD_PARAM;
   }
   if (kclass == 0 && !(tuning && (tuning->chunk > 0 || tuning->tile_p > 0 || tuning->tile_q > 0)))
-    kclass = untuned_class(prs);
+    kclass = untuned_class(instances, prs);
   if (maxC > kBatchMaxC[kclass]) return kclass == 0 ? GGDT_ERR_BAD_PARAM : GGDT_ERR_UNSUPPORTED;
   int rc = check_device();
   if (rc) return rc;
@@ -283,19 +380,10 @@ int ggdt_batched_plan(const ggdt_instance* instances, int n, const ggdt_tuning* 
 
   // Split the co-resident workgroups: one each, then greedily to the instance
   // with the largest remaining cost while it has tiles left to spread.
-  std::vector<int> w(n, 1);
-  std::vector<double> cost(n);
-  for (int i = 0; i < n; ++i) cost[i] = instance_cost(passes[i], 1);
-  int used = n;
-  while (used < cap) {
-    int best = -1;
-    for (int i = 0; i < n; ++i)
-      if (w[i] < max_tiles_of(passes[i]) && !passes[i].empty() && (best < 0 || cost[i] > cost[best])) best = i;
-    if (best < 0) break;
-    ++w[best];
-    cost[best] = instance_cost(passes[best], w[best]);
-    ++used;
-  }
+  std::vector<int> most(n);
+  for (int i = 0; i < n; ++i) most[i] = max_tiles_of(passes[i]);
+  const std::vector<int> w =
+      split_workgroups(n, cap, most, [&](int i, int k) { return instance_cost(passes[i], k); });
 
   // Workspace: header, class words, counters, exchange words per instance.
   ggdt_plan* plan = new ggdt_plan();
@@ -372,10 +460,8 @@ int ggdt_batched_plan(const ggdt_instance* instances, int n, const ggdt_tuning* 
     // (single-channel volumes: room for four tiles of the layout changes)
     const size_t blds0 = batched_bwd_lds_bytes(maxC2, maxC3), lds4 = (size_t)4 * 64 * 65 * 4;
     const size_t blds = bclass == 0 && blds0 < lds4 ? lds4 : blds0;
-    // class 0: the smaller tiles where every tile still has a CU, as in the forward
-    const int small = bclass == 0 ? untuned_class(prs) : 0;
-    const int btp = small == 3 || small == 4 ? kBatchTP3[small] : kTP3;
-    const int btq = small == 3 || small == 4 ? kBatchTQ3[small] : kTQ3;
+    int btp = kTP3, btq = kTQ3;
+    if (bclass == 0) reverse_tile(prs, &btp, &btq);
     int bcap = blds <= kMaxLdsBytes ? batched_bwd_capacity(bclass, btp, btq, blds) : 0;
     if (tuning && tuning->wg_per_cu > 0 && bcap > 0) {
       int dev = 0, cus = 0;
@@ -507,19 +593,10 @@ int ggdt_batched_plan(const ggdt_instance* instances, int n, const ggdt_tuning* 
           }
         }
       }
-      std::vector<int> bw(n, 1);
-      std::vector<double> bc(n);
-      for (int i = 0; i < n; ++i) bc[i] = instance_cost(bgeo[i], 1);
-      int bused = n;
-      while (bused < bcap) {
-        int best = -1;
-        for (int i = 0; i < n; ++i)
-          if (!bgeo[i].empty() && bw[i] < max_tiles_of(bgeo[i]) && (best < 0 || bc[i] > bc[best])) best = i;
-        if (best < 0) break;
-        ++bw[best];
-        bc[best] = instance_cost(bgeo[best], bw[best]);
-        ++bused;
-      }
+      std::vector<int> bmost(n);
+      for (int i = 0; i < n; ++i) bmost[i] = max_tiles_of(bgeo[i]);
+      const std::vector<int> bw =
+          split_workgroups(n, bcap, bmost, [&](int i, int k) { return instance_cost(bgeo[i], k); });
       int bwg0 = 0, pass0 = 0;
       for (int i = 0; i < n; ++i) {
         BatchInst bi = plan->h_insts[i];

@@ -50,3 +50,44 @@ def test_reverse_of_large_volumes(shape, lam):
         rgi, rgm = oracle.backward(c["image"], to_host(rec), W, *args, "f32")
         same(grads[0][1], rgm, "dL/dM")
         same(grads[0][0], rgi, "dL/dI")
+
+
+def batch_of(shapes, lam, iterations=1, seed=120):
+    cs = [synth.small_case(s, C=1, seed=seed + i, lam=lam, iterations=iterations) for i, s in enumerate(shapes)]
+    return cs, [dict(image=to_dev(c["image"]), softmask=to_dev(c["mask"]), spacing=c["spacing"], v=c["v"], lam=c["lam"],
+                     iterations=iterations) for c in cs]
+
+
+# 24 x 24 tiles where the passes have several tiles a workgroup for most of their
+# planes, and not where only the few planes of a short axis have
+@pytest.mark.parametrize("shape,n,lam,wide", [((400, 400, 8), 2, 1.0, False), ((400, 400, 8), 2, 0.5, False),
+                                              ((64, 200, 200), 4, 0.5, False), ((64, 200, 200), 4, 1.0, False),
+                                              ((150, 150, 150), 6, 0.5, True), ((40, 410, 410), 4, 1.0, True)], ids=str)
+def test_batch_takes_wide_tiles(shape, n, lam, wide):
+    from paper_2208_00001_amd.batched import BatchedPlan
+    img, m = torch.rand(shape, device=DEV), torch.ones(shape, device=DEV)
+    inst = [dict(image=img, softmask=m, spacing=(1.0, 1.0, 1.0), v=1e10, lam=lam, iterations=1) for _ in range(n)]
+    size = {}
+    for name, tuning in (("own", None), ("16", dict(tile_p=16)), ("24", dict(tile_p=24))):
+        plan = BatchedPlan(inst, tuning)
+        size[name] = plan.workspace.numel()
+        plan.close()
+    assert size["16"] != size["24"], "the exchange words do not tell the tiles apart"
+    assert size["own"] == size["24" if wide else "16"]
+
+
+# batches that the plan gives 16 x 16, 24 x 24, 8 x 16 and 8 x 8 tiles, some with images
+@pytest.mark.parametrize("shapes", [[(20, 40, 44)] * 30, [(20, 40, 44)] * 56 + [(70, 300), (33, 40)] * 2,
+                                    [(30, 31, 29)] * 24 + [(140, 50)], [(30, 29, 31)] * 6 + [(9, 30, 1)]],
+                         ids=["16x16", "24x24", "8x16", "8x8"])
+@pytest.mark.parametrize("lam", [0.5, 1.0])
+def test_batch_classes(shapes, lam):
+    from paper_2208_00001_amd.batched import BatchedPlan
+    cs, inst = batch_of(shapes, lam)
+    plan = BatchedPlan(inst)
+    plan.run()
+    plan.check()
+    for c, d in zip(cs, plan.inst):
+        ref = oracle.ggdt(c["image"], c["mask"], c["spacing"], c["v"], c["lam"], 1, "f32")
+        same(to_host(d["out"]), ref, c["name"])
+    plan.close()
