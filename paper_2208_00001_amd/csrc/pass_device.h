@@ -152,23 +152,6 @@ __device__ __forceinline__ int outside(int pp, int qq, int p0, int q0) {
   return max(dp, dq);
 }
 
-// Correctly rounded square root of x in [2^-96, FLT_MAX] from the hardware's
-// reciprocal root y: g = x y is within a few ulp of the root, d = x - g^2 is
-// exact up to one rounding, and g + d y / 2 rounds to the nearest (one Newton
-// step; Markstein's form for fused multiply-add).  For the correctly rounded y
-// it gives sqrtf(x) for every x; for y one ulp off, for all but five mantissas
-// (checked on the host), and with this chip's v_rsq_f32 for every float of the
-// range (all 1.88e9 of them compared with sqrtf on the GPU; the five mantissas
-// are in the tests).  In this range sqrtf as built here has the same bits (its
-// lowering scales only arguments below 2^-96 and special-cases only zero and
-// infinity).  5 instructions instead of the 9 that correct a hardware square
-// root by the signs of two residuals (sqrt_round_fix): the general edge cost
-// is what bounds a pass at lambda in (0, 1).
-__device__ __forceinline__ float sqrt_from_rsq(float x, float y) {
-  const float g = x * y, h = 0.5f * y;
-  return fmaf(fmaf(-g, g, x), h, g);
-}
-
 // sqrtf(x) for the general modes.  ZERO: x may be +0 (lambda 1 with several
 // channels; then every other x is at least 2^-94): the clamped reciprocal root
 // leaves g = +0 there.
