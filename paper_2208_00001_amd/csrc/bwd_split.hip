@@ -1,6 +1,7 @@
 // Kernels of the single-instance reverse: the scan of a pass and the edge
 // gradients of its voxels (bwd_scan.h says why they are two).
 #include "bwd_scan.h"
+#include "edge_grid.h"
 
 namespace ggdt {
 namespace {
@@ -128,15 +129,17 @@ __device__ __forceinline__ void edge_voxel(const BwdDesc& g, const EdgeDesc& s, 
 }
 
 template <int ND, int NCH>
-__global__ __launch_bounds__(256) void bwd_edge_kernel(BwdDesc g, EdgeDesc s, const unsigned* words) {
+__global__ __launch_bounds__(kEdgeThreads) void bwd_edge_kernel(BwdDesc g, EdgeDesc s, const unsigned* words) {
   __shared__ float sA[9];
   if (threadIdx.x < 9) sA[threadIdx.x] = g.A[threadIdx.x];
   __syncthreads();
-  const int col = blockIdx.x * 64 + (threadIdx.x & 63);
-  if (col >= s.d2) return;
+  const unsigned ucol = s.col0 + blockIdx.x * kEdgeCols + (threadIdx.x & (kEdgeCols - 1));
+  if (ucol >= (unsigned)s.d2) return;
+  const int col = (int)ucol;
   const unsigned* cls = words + kWordClass;
   const long long rows = (long long)(g.N / s.d2);
-  for (long long row = (long long)blockIdx.y * 4 + (threadIdx.x >> 6); row < rows; row += (long long)gridDim.y * 4) {
+  for (long long row = (long long)blockIdx.y * kEdgeRows + (threadIdx.x / kEdgeCols); row < rows;
+       row += (long long)gridDim.y * kEdgeRows) {
     if (g.mode == kModeLam0)
       edge_voxel<ND, kModeLam0, NCH>(g, s, sA, col, row);
     else if (NCH == 1 && g.mode == kModeLam1C1 && fast_mode_ok(kModeLam1C1, ld_relaxed(cls)))
@@ -181,14 +184,19 @@ hipError_t launch_scan_row(const BwdDesc& d, unsigned* words, unsigned long long
 }
 
 template <int ND>
-hipError_t launch_edges(const BwdDesc& g, const EdgeDesc& s, const unsigned* words, hipStream_t stream) {
+hipError_t launch_edges(const BwdDesc& g, EdgeDesc s, const unsigned* words, hipStream_t stream) {
   const long long rows = (long long)(g.N / s.d2);
-  const long long by = (rows + 3) / 4;
-  const dim3 grid((unsigned)((s.d2 + 63) / 64), (unsigned)(by < 32768 ? by : 32768));
   auto fn = g.C == 1 ? bwd_edge_kernel<ND, 1>
                      : (g.C == 2 ? bwd_edge_kernel<ND, 2> : (g.C == 3 ? bwd_edge_kernel<ND, 3> : bwd_edge_kernel<ND, 0>));
-  hipLaunchKernelGGL(fn, grid, dim3(256), 0, stream, g, s, words);
-  return hipGetLastError();
+  for (unsigned col0 = 0; col0 < (unsigned)s.d2; col0 += kEdgeLaunchCols) {
+    unsigned gx, gy;
+    edge_grid((unsigned)s.d2, col0, rows, &gx, &gy);
+    s.col0 = col0;
+    hipLaunchKernelGGL(fn, dim3(gx, gy), dim3(kEdgeThreads), 0, stream, g, s, words);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace

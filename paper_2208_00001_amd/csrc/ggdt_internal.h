@@ -218,6 +218,7 @@ struct EdgeDesc {
   int first;    // gI is not read (zero so far)
   int last;     // out = v * abar
   float v;
+  unsigned col0 = 0;  // first column of the launch (set by launch_bwd_edges)
 };
 hipError_t launch_bwd_scan(const BwdDesc& d, int ndim, unsigned* words, unsigned long long spin_limit,
                            hipStream_t stream);
