@@ -91,3 +91,30 @@ def test_batch_classes(shapes, lam):
         ref = oracle.ggdt(c["image"], c["mask"], c["spacing"], c["v"], c["lam"], 1, "f32")
         same(to_host(d["out"]), ref, c["name"])
     plan.close()
+
+
+def sides_of(kind, shape):
+    """Transforms that a composed operation runs side by side, from the workspace it asks for."""
+    from paper_2208_00001_amd import binding as B
+    lib, dims, vol = B.load_library(), (ctypes.c_int * 3)(*shape), round256(4 * int(np.prod(shape)))
+    n = (lib.ggdt_signed_workspace_bytes if kind == "signed" else lib.ggdt_gsf_workspace_bytes)(3, dims, 1)
+    words = lib.ggdt_workspace_min_bytes(3, dims, 1) - 256  # exchange words of one transform
+    found = [s for s in (2, 4) if n == round256(256 + s * words) + (7 if kind == "gsf" else 2) * vol + (s + 1) * vol]
+    return found[0] if found else 1
+
+
+# the filter's four transforms in pairs, whose masks take turns on one set of
+# copies; and four together whose tiles outnumber the chip's workgroups on an axis
+# of several chunks
+@pytest.mark.parametrize("shape,sides", [((84, 86, 161), 2), ((26, 140, 150), 4)], ids=str)
+@pytest.mark.parametrize("lam", [0.6, 1.0])
+def test_filter_side_by_side(shape, sides, lam):
+    from paper_2208_00001_amd import binding as B
+    assert sides_of("gsf", shape) == sides and sides_of("signed", shape) == 2
+    c = synth.small_case(shape, C=1, seed=160, lam=lam, iterations=1)
+    m = (c["mask"] > 0).astype(np.float32)
+    m[tuple(slice(s // 4, s // 2) for s in shape)] = 0.0
+    img, md = to_dev(c["image"]), to_dev(m)
+    print(f"case {c['name']} lam={lam} sides={sides}", flush=True)
+    got = B.ggdt_gsf(img, md, 0.3, 0.2, c["spacing"], c["v"], c["lam"], 1, check=True)
+    same(to_host(got), oracle.gsf(c["image"], m, 0.3, 0.2, c["spacing"], c["v"], c["lam"], 1), "filter")
