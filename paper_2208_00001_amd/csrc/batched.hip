@@ -186,8 +186,10 @@ size_t lds_for(int C, bool has2d, bool has3d) {
   return b;
 }
 
-// Single-channel batches: the pairs of the thread-per-cell pass, the teams'
-// costs, and four tiles of the layout changes.
+// Single-channel batches, whatever their instances: the pairs of the thread-per-cell
+// pass, the teams' costs, and four tiles of the layout changes.  (The kernels' 119
+// to 121 registers allow one workgroup of 1024 threads a CU, so less LDS for
+// batches without images would not add one.)
 constexpr size_t kTeamBatchLds = sizeof(float) * (kBatchTeams * 2 * team_chunk(kBatchK2[0]) + 1);
 constexpr size_t kLayoutLds = sizeof(float) * 4 * kTrTileElems;
 constexpr size_t kCellBatchLds = kTeamBatchLds > kLayoutLds ? kTeamBatchLds : kLayoutLds;

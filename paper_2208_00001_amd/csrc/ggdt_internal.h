@@ -184,9 +184,10 @@ constexpr int kCellTP = 16, kCellTQ = 16, kCellK = 8, kCellMaxC = 3;
 
 // Batched kernel classes.  Single-channel batches run thread-per-cell passes on
 // volumes (their tile per class) and teams (pass_team.h) on images: 0 and 2 may
-// also be asked for by a tuning; 3 and 4 have smaller tiles, for batches whose
-// tiles then still have a CU each; 2 has less halo arithmetic for twice the
-// exchanges, for batches with several tiles per CU.  Class 1, the tile passes
+// also be asked for by a tuning; 3 and 4 have smaller tiles and shorter plane
+// steps, for batches with few tiles per CU; 2 has less halo arithmetic for twice the
+// exchanges (1.27 computed cells per voxel update instead of 2.15, in the same box
+// of 1024), for batches with several tiles per CU.  Class 1, the tile passes
 // for up to 4 channels.  Chunk lengths (3D / 2D), 3D tile, channel limit:
 constexpr int kBatchClasses = 5;
 constexpr int kBatchK3[kBatchClasses] = {8, 4, 4, 8, 8};

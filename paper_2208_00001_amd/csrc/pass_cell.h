@@ -20,15 +20,8 @@
 namespace ggdt {
 namespace dev {
 
-
 constexpr int kCellBQ = kCellTQ + 2 * kCellK;          // 32: box row length
 constexpr int kCellThreads = kCellBQ * kCellBQ;         // 1024: one thread per box cell
-// Scan-contiguous layout: per box cell a run of kCellSC consecutive memory
-// positions along the scan axis (K + 1 planes and up to 3 alignment slots,
-// starting at a multiple of 4), and the own cells' results at an odd stride.
-constexpr int kCellSC = 4 * ((kCellK + 4 + 3) / 4);    // 12
-constexpr int kCellSCR = kCellK + 1;                     // 9
-constexpr int kCellStage = kCellThreads * kCellSC;       // floats of one staged array
 
 // Tile, chunk and box of a pass, and the threads of its workgroups.
 template <int TP_, int TQ_, int KC>
@@ -41,6 +34,9 @@ struct CellGeom {
   // room on ceil(waves / 4) slots of one SIMD, which a count that is no
   // multiple of 4 waves would not show.
   static constexpr int NTCAP = (NB + 255) / 256 * 256;
+  // Scan-contiguous layout: per box cell a run of SC consecutive memory positions
+  // along the scan axis (K + 1 planes and up to 3 alignment slots, starting at a
+  // multiple of 4), and the own cells' results at an odd stride.
   static constexpr int SC = 4 * ((KC + 4 + 3) / 4);
   static constexpr int SCR = KC + 1;
   static constexpr int STAGE = NB * SC;
@@ -50,10 +46,6 @@ struct CellGeom {
 using CellGeomBase = CellGeom<kCellTP, kCellTQ, kCellK>;
 using CellGeomMid = CellGeom<8, 16, kCellK>;    // 24 x 32 box, 12 waves
 using CellGeomSmall = CellGeom<8, 8, kCellK>;   // 24 x 24 box, 9 waves
-// The same box of 1024 cells also holds a 24 x 24 tile with K = 4 (batched
-// launches may choose it): 1.27 computed cells per voxel update instead of
-// 2.15, for twice the exchanges.
-using CellGeomWide = CellGeom<24, 24, 4>;
 // A geometry in a workgroup of kCellThreads threads, whatever its box needs
 // (batched launches): the threads past the box only meet the barriers.
 template <class Geo>
@@ -92,9 +84,9 @@ __device__ __forceinline__ void step_barrier() {
 struct CellLds {
   float2* pair;  // 2 x threads: (D, I of channel 0)
   float* chan;   // 2 x (NCH - 1) x threads: the further channels (multi-channel volumes only)
-  float* stD;    // kCellStage (scan-contiguous layout only)
-  float* stI;    // kCellStage
-  float* res;    // kCellTP * kCellTQ * kCellSCR
+  float* stD;    // Geo::STAGE (scan-contiguous layout only)
+  float* stI;    // Geo::STAGE
+  float* res;    // Geo::RES
   int* fail;     // one word: item number + 1 of a bounded wait that gave up
 };
 
