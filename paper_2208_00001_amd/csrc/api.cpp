@@ -349,8 +349,13 @@ int enqueue_forward(const Problem& pr, const float* image, const float* mask, co
 }
 
 // How many of n transforms of one image run side by side: a power of two.  Of an
-// image, all: its passes take at most 64 waves of the chip's 1024 SIMDs.  Of a
-// volume, as many as shorten the whole by the time of a plane step on the tile
+// image, all: a pass is one team of four waves per 32 columns and transform, 64
+// teams at 2048 columns, and a chain of rows whatever their number.  Where the
+// teams of all transforms outnumber the CUs they share them, and beyond what is
+// resident a team walks several tiles; the whole is still the faster.  ms one
+// after the other on one wave per tile / side by side: filter of 2048^2 at lambda 0,
+// 0.5 13.2 / 3.7, 22.3 / 3.9; of 4096^2 26.8 / 7.6, 45.4 / 8.5; of 500 x 20000 68.9 /
+// 18.1, 118 / 19.0.  Of a volume, as many as shorten the whole by the time of a plane step on the tile
 // that cell_tile gives them (0.73, 0.75 and 0.93 us on 8 x 8, 8 x 16 and 16 x 16
 // tiles at lambda in (0, 1)), times the tiles a CU then has.
 int sides_for(const Problem& pr, int n) {

@@ -307,10 +307,11 @@ int ggdt_batched_plan(const ggdt_instance* instances, int n, const ggdt_tuning* 
 
   // Pass descriptors (schedule order) per instance, chunk length of the kernel
   // class.  As in the plain forward, the passes along the last axis of a
-  // single-channel volume without records run on scan-major copies of D and
-  // of the image in the workspace: layout changes (descriptors with op !=
-  // kOpPass) move the image there before the first pass and D there and back
-  // around each iteration's last two passes.  Workspace offsets not yet known
+  // single-channel volume run on scan-major copies of D and of the image in
+  // the workspace: layout changes (descriptors with op != kOpPass) move the
+  // image there before the first pass, D there and back around each
+  // iteration's last two passes, and a pass's records to the array layout after
+  // it.  Workspace offsets not yet known
   // are marked kSlotD / kSlotImage and filled in with the layout below.
   constexpr long long kSlotD = -2, kSlotImage = -3, kSlotRec = -4;
   std::vector<std::vector<PassDesc>> passes(n);

@@ -3,10 +3,11 @@
 // A pass along the contiguous memory axis of a C-order volume reads each
 // voxel's planes as consecutive elements of one memory row, which the plane
 // kernels can only gather by short runs.  The forward schedule therefore runs
-// the two passes along the last axis of a single-channel volume on a copy laid
-// out [W][D][H] (the scan axis slowest, H contiguous), where they are ordinary
-// strided passes, and moves D into and out of that layout once per iteration.
-// Moving values is exact, so the passes see the same numbers.
+// the two passes along the last axis of a volume of up to three channels on a
+// copy laid out [W][D][H] (the scan axis slowest, H contiguous), where they are
+// ordinary strided passes, and moves D into and out of that layout once per
+// iteration; the reverse does so with what its passes read and write.  Moving
+// values is exact, so the passes see the same numbers.
 #include "ggdt_internal.h"
 #include "layout.h"
 

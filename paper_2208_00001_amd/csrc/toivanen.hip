@@ -27,8 +27,9 @@
 // well would read each other both ways through the offsets (-1, +1, *) and
 // (0, -1, *), a cycle.)  Progress is the number of steps (hyperplanes) a block
 // has completed since the launch, published every few steps and at the end of
-// each sweep (release at agent scope by one thread, after a workgroup
-// barrier); a block that needs more than it has seen polls and acquires.  A
+// each sweep (release at agent scope by one thread after a workgroup barrier:
+// the barrier orders the other waves' stores before it at workgroup scope, and
+// the release carries them on); a block that needs more than it has seen polls and acquires.  A
 // block skips the hyperplanes that miss all its rows.  The same waits order
 // the sweeps: a block's first step of a sweep needs its neighbour to have
 // finished the previous sweep, and that neighbour is the one block that read
@@ -75,8 +76,10 @@ __device__ __forceinline__ bool wait_progress(unsigned long long* prog, int dep,
   return true;
 }
 
-// Thread 0, after a workgroup barrier that drained every wave's stores:
-// publish the block's completed steps.
+// Thread 0, after a workgroup barrier: publish the block's completed steps.  The
+// barrier does not wait for the other waves' stores; it orders them before this
+// thread's release at workgroup scope, and the release at agent scope, being
+// cumulative, makes them visible before the count.
 __device__ __forceinline__ void publish_progress(unsigned long long* prog, int b, unsigned long long steps) {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
   __hip_atomic_store(prog + b, steps, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -189,16 +192,17 @@ __global__ __launch_bounds__(kToivThreads) void toivanen_kernel(ToivDesc d, unsi
 // last S steps of its rows' values of D and of the image in LDS rings (slot =
 // step mod S; a preceding neighbour lies at most 7 steps back in a volume, 3
 // in an image), and the neighbour block's rows it reads, its ghost rows, in
-// rings of their own.  A voxel's candidates then come from LDS; the only
-// global accesses of a step are loads issued one step ahead (the row's own D
-// from the previous sweep and its image value, and one ghost voxel per ghost
-// row) and the store of the result.  Steps meet at an LDS barrier; every
-// `publish` steps a full workgroup barrier drains the stores before the
-// progress is published.  Thread 0 waits, at the end of each step, for the
+// rings of their own.  A voxel's candidates then come from LDS.  A row's own D
+// (from the previous sweep) and image values move four steps at a time: one
+// 16-byte load per array, four steps ahead, and one 16-byte store of the
+// results; a step itself only loads one ghost voxel per ghost row, a step ahead.
+// Steps meet at an LDS barrier.  Every `publish` steps the results not yet stored
+// are, and a full workgroup barrier comes before the publication
+// (publish_progress).  Thread 0 waits, at the end of each step, for the
 // neighbour's progress that the next step's ghost load needs.  The offsets and
-// the sweep direction are compile-time constants, so a candidate costs its
-// two LDS reads and its arithmetic; the ring slot of an offset is the same
-// for every thread.
+// the sweep direction are compile-time constants, so a candidate costs one 8-byte
+// LDS read (and one per further channel) and its arithmetic; the ring slot of an
+// offset is the same for every thread.
 
 // The preceding neighbours in the forward raster order, in the order the
 // host's edge constants A_j follow: (-1, *, *), (0, -1, *), (0, 0, -1).
