@@ -199,6 +199,12 @@ __device__ __forceinline__ bool run_bwd_pass_cell(const BwdDesc* gp, unsigned lo
     for (int w = 0; w < NRW; ++w) rec[w] = 0u;
 #pragma unroll
     for (int m = 0; m <= K; ++m) rec[m >> 2] |= (unsigned)nR[m] << (8 * (m & 3));
+    // Bytes of records from another schedule may exceed 9: cut to 15, whose parent
+    // (three rows on at most) still lies in the box of a cell within distance 1.
+    // (Testing each record where a step uses it costs 2 % of a pass at lambda 1.)
+    static_assert(K >= 4, "rows of the box past a cell next to the tile");
+#pragma unroll
+    for (int w = 0; w < NRW; ++w) rec[w] &= 0x0f0f0f0fu;
 
     // Plane 0 of the chunk: abar_in of the pass's last plane in chunk 0, else
     // the state the previous chunk published (this tile's and its neighbours').

@@ -375,7 +375,8 @@ __device__ __forceinline__ bool run_bwd_pass(const BwdDesc* gp, unsigned long lo
                     }
                   }
                 }
-              if (ry != 0 && i + 2 <= mtop) {
+              // (a record beyond the offsets only comes from another schedule: skip it)
+              if (ry >= 1 && ry <= (NDIM == 3 ? 9 : 3) && i + 2 <= mtop) {
                 const int j = ry - 1;
                 const int dp = NDIM == 3 ? j / 3 - 1 : 0, dq = (NDIM == 3 ? j % 3 : j) - 1;
                 const float* spI = StI + sidx(i + 2, ly + dp * BQ + dq);  // parent y' = y + delta_j

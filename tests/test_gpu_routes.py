@@ -118,3 +118,30 @@ def test_filter_side_by_side(shape, sides, lam):
     print(f"case {c['name']} lam={lam} sides={sides}", flush=True)
     got = B.ggdt_gsf(img, md, 0.3, 0.2, c["spacing"], c["v"], c["lam"], 1, check=True)
     same(to_host(got), oracle.gsf(c["image"], m, 0.3, 0.2, c["spacing"], c["v"], c["lam"], 1), "filter")
+
+
+@pytest.mark.parametrize("shapes", [[(20, 33, 40), (9, 50, 41)], [(20, 33, 40), (70, 65)], [(130, 70)]], ids=str)
+@pytest.mark.parametrize("lam", [0.0, 0.6, 1.0])
+def test_records_beyond_the_offsets(shapes, lam):
+    """Record bytes that name no offset (records of another schedule) index nothing and
+    end a voxel's path, in the batched reverses as in the plain one (the image
+    gradient is then unspecified).  Bytes from 16 run too, with no value asserted."""
+    from paper_2208_00001_amd import binding as B
+    from paper_2208_00001_amd.batched import BatchedPlan
+    rng = np.random.default_rng(170)
+    cs = [synth.small_case(s, C=1, seed=170 + i, lam=lam, iterations=1, soft=True, v=10.0) for i, s in enumerate(shapes)]
+    W = [to_dev(rng.standard_normal(s).astype(np.float32)) for s in shapes]
+    plan = BatchedPlan([dict(image=to_dev(c["image"]), softmask=to_dev(c["mask"]), spacing=c["spacing"], v=c["v"],
+                             lam=c["lam"], iterations=1, records=True, grad_out=w) for c, w in zip(cs, W)])
+    plan.run()
+    plan.check()
+    for top in (256, 16):
+        for rec in plan.records:
+            other = rng.integers(10, top, size=tuple(rec.shape)).astype(np.uint8)
+            rec.copy_(torch.where(to_dev(rng.random(tuple(rec.shape)) < 0.2), to_dev(other), torch.clamp(rec, max=9)))
+        grads = plan.backward()
+        plan.check()
+    for c, d, w, (gi, gm) in zip(cs, plan.inst, W, grads):
+        _, pm = B.ggdt_backward(d["image"], d["records"], w, c["spacing"], c["v"], c["lam"], 1, check=True)
+        same(to_host(gm), to_host(pm), "dL/dM")
+    plan.close()
