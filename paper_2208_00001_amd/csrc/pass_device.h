@@ -110,14 +110,11 @@ __device__ __forceinline__ void st64_relaxed(unsigned long long* p, unsigned lon
 }
 
 // The value of the word at `a` once it is published under `epoch`: polled up to
-// `limit` times, then the abort word is set; *fail when the wait gave up.  A poll is
-// counted while its load is on the way.
+// `limit` times, then the abort word is set; *fail when the wait gave up.
 __device__ __forceinline__ float wait_word(const unsigned long long* a, unsigned epoch, unsigned* words,
                                            unsigned long long limit, int* fail) {
   unsigned long long wv = ld64_relaxed(a);
   while (__builtin_expect((unsigned)(wv >> 32) != epoch, 0)) {
-    __builtin_amdgcn_s_sleep(1);
-    wv = ld64_relaxed(a);
     if (!take_poll(&limit)) {
       __hip_atomic_fetch_or(words + kWordAbort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       *fail = 1;
@@ -128,6 +125,8 @@ __device__ __forceinline__ float wait_word(const unsigned long long* a, unsigned
       *fail = 1;
       break;
     }
+    __builtin_amdgcn_s_sleep(1);
+    wv = ld64_relaxed(a);
   }
   return __uint_as_float((unsigned)wv);
 }
