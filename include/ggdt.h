@@ -289,7 +289,9 @@ int ggdt3d_noalloc(const float* image, const float* softmask, const float* spaci
 int ggdt_workspace_status(const void* workspace, hipStream_t stream);
 
 /* Debug knob: upper bound on polls of one inter-workgroup wait before the
- * watchdog fires (default 2^21).  Process-wide; 0 restores the default. */
+ * watchdog fires (default 2^21).  Process-wide; 0 restores the default.  The waits
+ * inside a pass take at most 2^31 - 1 polls (a quarter of an hour and more)
+ * whatever the bound; counting 64 bits there slows passes down. */
 void ggdt_set_spin_limit(unsigned long long polls);
 
 /* Profiling (process-wide, not thread-safe).  After ggdt_profile_begin(n) the

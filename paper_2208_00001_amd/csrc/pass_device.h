@@ -31,7 +31,6 @@
 #pragma once
 
 #include "ggdt_internal.h"
-#include "poll_budget.h"
 #include "sqrt_fix.h"
 
 namespace ggdt {
@@ -114,14 +113,17 @@ __device__ __forceinline__ void st64_relaxed(unsigned long long* p, unsigned lon
 __device__ __forceinline__ float wait_word(const unsigned long long* a, unsigned epoch, unsigned* words,
                                            unsigned long long limit, int* fail) {
   unsigned long long wv = ld64_relaxed(a);
+  const unsigned most = limit < 0x7fffffffull ? (unsigned)limit : 0x7fffffffu;
+  unsigned polls = 0;
   while (__builtin_expect((unsigned)(wv >> 32) != epoch, 0)) {
-    if (!take_poll(&limit)) {
+    ++polls;
+    if (polls > most) {
       __hip_atomic_fetch_or(words + kWordAbort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       *fail = 1;
       break;
     }
     // the abort word costs a memory round trip: look at it every 32 polls
-    if ((limit & 31u) == 0u && ld_relaxed(words + kWordAbort) != 0u) {
+    if ((polls & 31u) == 0u && ld_relaxed(words + kWordAbort) != 0u) {
       *fail = 1;
       break;
     }
