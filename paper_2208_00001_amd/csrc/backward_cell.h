@@ -30,9 +30,13 @@ namespace dev {
 
 // LDS of the reverse pass: two planes of (abar, record bits), two of (I,
 // coefficient) (read by own cells only), two image planes (a step's grandparent
-// plane), one fail word.
+// plane), one fail word.  Bytes of records from another schedule may exceed 9; the
+// parent's place that a byte of 255 names lies up to 83 rows on, and the area ends
+// past it, so that such a record reads LDS of the workgroup's own and no step has
+// to look for it (masking or testing the records costs 0.5 to 2 % of a pass).
 constexpr size_t kBwdCellLdsBytes = sizeof(float2) * 4 * kCellThreads + sizeof(float) * 2 * kCellThreads +
-                                    sizeof(int);
+                                    sizeof(int) + sizeof(float) * (84 * kCellBQ + 2);
+static_assert(254 / 3 - 1 <= 84, "rows past a cell that a record byte can name");
 // record bits of a published cell: the record (0 or 1 + j), and kCoefValid
 // when its parent edge has w > 0 (its coefficient then enters the parent's Ibar)
 constexpr int kCoefValid = 0x100;
@@ -199,12 +203,6 @@ __device__ __forceinline__ bool run_bwd_pass_cell(const BwdDesc* gp, unsigned lo
     for (int w = 0; w < NRW; ++w) rec[w] = 0u;
 #pragma unroll
     for (int m = 0; m <= K; ++m) rec[m >> 2] |= (unsigned)nR[m] << (8 * (m & 3));
-    // Bytes of records from another schedule may exceed 9: cut to 15, whose parent
-    // (three rows on at most) still lies in the box of a cell within distance 1.
-    // (Testing each record where a step uses it costs 2 % of a pass at lambda 1.)
-    static_assert(K >= 4, "rows of the box past a cell next to the tile");
-#pragma unroll
-    for (int w = 0; w < NRW; ++w) rec[w] &= 0x0f0f0f0fu;
 
     // Plane 0 of the chunk: abar_in of the pass's last plane in chunk 0, else
     // the state the previous chunk published (this tile's and its neighbours').
