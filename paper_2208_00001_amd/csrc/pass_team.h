@@ -8,9 +8,9 @@
 // wave advances the current chunk: a step of it is three additions and minima,
 // whatever the channel count.  Tiles, chunks, exchange words and the lanes'
 // cells are described in pass_row.h.  ns per row at 2048 x 2048, the costs inside
-// the chain / here: one channel at lambda 0.5 226 / 111, at 1 150 / 111; three
-// channels at 0.5 283 / 123; a chunk of 16 rows takes 1.8 us, 0.5 of it the
-// neighbours' words' latency.
+// the chain / here (the mean of both axes): one channel at lambda 0.5 226 / 111, at
+// 1 150 / 111, at 0 137 / 106; three channels at 0.5 283 / 119; a chunk of 16 rows
+// takes 1.7 to 1.9 us, 0.5 of it the neighbours' words' latency.
 #pragma once
 
 #include "pass_cell.h"
